@@ -294,8 +294,7 @@ GemmPlan frag_plan(int M, int N, int K, int geglu, int cus, bool allow_split, bo
   // convolutions: a partly filled round costs more than its average load per CU (the
   // CUs that hold one more unit finish last)
   const double fill_penalty = conv ? 0.25 : 0.0;
-  GemmPlan best{128, 256, 0};
-  best.stages = 3;
+  GemmPlan best{128, 256};
   best.frag = 1;
   double best_t = 1e300;
   const int nk = K / 64;
@@ -332,7 +331,7 @@ GemmPlan frag_plan(int M, int N, int K, int geglu, int cus, bool allow_split, bo
   // layers run as fast or faster on five waves
   if (best.bm == 128 && best.bn == 160 &&
       (conv || (long long)ceil_div(M, 128) * ceil_div(N, 160) * best.split > cus))
-    best.stages = 5;
+    best.x5 = 1;
   // 128 x 256 linear tiles (two workgroups per CU) whose count leaves a last round at most
   // half full: those last whole column bands run as 64-row tiles over every CU
   if (!conv && best.bm == 128 && best.bn == 256 && best.split == 1) {
@@ -350,8 +349,8 @@ template <typename T>
 GemmPlan gemm_plan(int M, int N, int K, int geglu, int cus, bool allow_split, bool fused_reduce, bool conv) {
   if (sizeof(T) == 2 && gemm_frag_layout(N, K)) return frag_plan(M, N, K, geglu, cus, allow_split, fused_reduce, conv);
   const long long t128 = (long long)ceil_div(M, 128) * ceil_div(N, 128);
-  if (!geglu && t128 < cus) return GemmPlan{64, 64, 0};
-  return GemmPlan{128, 128, 0};
+  if (!geglu && t128 < cus) return GemmPlan{64, 64};
+  return GemmPlan{128, 128};
 }
 
 template <typename T> void gemm(const GemmParams& p, const GemmPlan& g, hipStream_t s) {

@@ -25,10 +25,7 @@
 //  - split-K: the units (tile, split) cover contiguous K ranges and write fp32 partial
 //    tiles; a second kernel sums the slabs in split order (deterministic) and applies
 //    the epilogue;
-//  - epilogue through LDS: each wave writes its accumulators to LDS and reads them back
-//    row-contiguous, so bias / residual loads and output stores are whole row segments
-//    of 64-256 bytes instead of 16-byte pieces of 32 different rows. The per-head V^T
-//    columns keep the register layout, where consecutive lanes are consecutive tokens.
+//  - epilogue from registers (wave_epilogue); the split-K slabs go through LDS as whole rows;
 //  - tiles go to XCDs in contiguous ranges (workgroup ids are dealt round-robin over the
 //    8 XCDs), ordered by column band, split, then row tile, so that the units sharing a
 //    band of B run on one XCD and share its L2;
@@ -81,64 +78,439 @@ template <int I, int NM, int NR, int NV> struct KSched {
   }
 };
 
-// Epilogue inputs and outputs of 8 consecutive columns [n, n + 8) of row m (n % 8 == 0).
-// The 16-byte forms need the whole group inside n_store, a leading dimension that keeps
-// every row's group 16-byte aligned and a 16-byte aligned base; otherwise element-wise,
-// with zeros (loads) or nothing (stores) past n_store.
 __device__ __forceinline__ bool aligned16(const void* q) {
   return (reinterpret_cast<__UINTPTR_TYPE__>(q) & 15) == 0;
 }
-__device__ __forceinline__ bool resid_vec8(const GemmParams& p) {
-  return aligned16(p.resid) && (p.ldr & (p.resid_f32 ? 3 : 7)) == 0;
+
+// ---------------------------------------------------------------- epilogue
+//
+// A wave's accumulators leave straight from registers. Lane l of a 32 x 32 block holds row
+// l % 32 and, in registers 4 g .. 4 g + 3, the four columns 8 g + 4 (l / 32) ... For bf16 one
+// v_permlane32_swap per dword exchanges the halves' pieces of two g, after which a lane holds
+// 8 consecutive columns (16 bytes); then, for both types, v_permlane16_swap trades 16-lane
+// rows between two such pieces, so that a store (and a residual load) covers 64 bytes of each
+// of 16 rows. The next block's residual is loaded before the current one is finished.
+//
+// What bounds it: every workgroup of a launch reaches its epilogue together and runs every
+// instruction of it once, so its time is instruction fetch and the store burst. Hence one
+// short path per kind of output. The previous form (through LDS, one path with run-time cases
+// and element-wise tails, about 25,000 instructions) took 5.1 us of a 128 x 128 tile's launch
+// and 13 us of a lone 128 x 256 tile's; measured whole launches, before -> after: QKV
+// 2048 x 3840 x 1280 32.3 -> 28.2 us, projection 2048 x 1280 x 1280 with an fp32 residual
+// 20.1 -> 17.8 us, FF-in 66.6 -> 63.1 us, 32768-row convolution 320 -> 320 77.9 -> 72.7 us.
+// Layouts the vector forms do not take (bases or leading dimensions that are not 16-byte
+// aligned, a V^T split inside a 32-column block or an odd sequence) go through LDS in a
+// rolled loop.
+
+// kinds of the vector path
+enum EpiKind { kEpiGeneric = 0, kEpiBf16, kEpiF32, kEpiGeglu };
+
+__device__ __forceinline__ bool bias_vec(const GemmParams& p) { return !p.bias || aligned16(p.bias); }
+
+// Uniform over the launch. Column blocks are whole (n_store is a multiple of 32, or of 4 and
+// equal to N for the slabs), so only row tails are masked.
+__device__ __forceinline__ int epi_kind(const GemmParams& p) {
+  if (p.n_store % 32 != 0 || !bias_vec(p) || !aligned16(p.out) || (p.wscale && !aligned16(p.wscale))) return kEpiGeneric;
+  if (p.geglu) return !p.out_f32 && p.ldo % 16 == 0 ? kEpiGeglu : kEpiGeneric;
+  if (p.out_fp8) return kEpiGeneric;
+  if (p.rowvec && (p.rowvec_ld % 4 != 0 || !aligned16(p.rowvec))) return kEpiGeneric;
+  if (p.resid && (!aligned16(p.resid) || p.ldr % 8 != 0)) return kEpiGeneric;
+  if (p.vt && (p.vt_col0 % 32 != 0 || p.vt_dp % 32 != 0 || p.vt_seq % 2 != 0 || p.vt_ld % 2 != 0 || p.out_f32 ||
+               p.rowvec || p.resid || (reinterpret_cast<__UINTPTR_TYPE__>(p.vt) & 3) != 0))
+    return kEpiGeneric;
+  if (p.out_f32) return p.ldo % 4 == 0 ? kEpiF32 : kEpiGeneric;
+  return p.ldo % 8 == 0 ? kEpiBf16 : kEpiGeneric;
 }
-__device__ __forceinline__ bool out_vec8(const GemmParams& p) {
-  return aligned16(p.out) && (p.ldo & (p.out_f32 ? 3 : 7)) == 0;
+
+__device__ __forceinline__ f32x4 ld_f4(const float* q) { return *reinterpret_cast<const f32x4*>(q); }
+
+__device__ __forceinline__ unsigned pack_bf16(float a, float b) {
+  const bf16x2 v = {static_cast<bf16>(a), static_cast<bf16>(b)};
+  return __builtin_bit_cast(unsigned, v);
 }
-__device__ __forceinline__ void load_rowvec8(const GemmParams& p, int m, int n, float v[8]) {
-  const float* r = p.rowvec + (long long)(m / p.rows_per_sample) * p.rowvec_ld + n;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) v[e] = n + e < p.n_store ? r[e] : 0.f;
+
+// v_permlane32_swap: lanes 32 - 63 of a and lanes 0 - 31 of b trade places.
+struct Pair {
+  unsigned a, b;
+};
+__device__ __forceinline__ Pair swap32(unsigned a, unsigned b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+  return Pair{r[0], r[1]};
 }
-__device__ __forceinline__ void load_resid8(const GemmParams& p, int m, int n, bool vec, float v[8]) {
-  const long long ro = (long long)m * p.ldr + n;
-  if (vec) {
-    if (p.resid_f32) {
-      const f32x4* r = reinterpret_cast<const f32x4*>(static_cast<const float*>(p.resid) + ro);
-      const f32x4 a = r[0], b = r[1];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        v[e] = a[e];
-        v[e + 4] = b[e];
-      }
-    } else {
-      const bf16x8 r = *reinterpret_cast<const bf16x8*>(static_cast<const bf16*>(p.resid) + ro);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] = static_cast<float>(r[e]);
-    }
-  } else {
-#pragma unroll
-    for (int e = 0; e < 8; ++e)
-      v[e] = n + e >= p.n_store ? 0.f
-             : p.resid_f32      ? static_cast<const float*>(p.resid)[ro + e]
-                                : static_cast<float>(static_cast<const bf16*>(p.resid)[ro + e]);
-  }
+
+// v_permlane16_swap: the odd 16-lane rows of a and the even ones of b trade places.
+__device__ __forceinline__ Pair swap16(unsigned a, unsigned b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+  return Pair{r[0], r[1]};
 }
-__device__ __forceinline__ void store8(const GemmParams& p, int m, int n, const float v[8], bool vec) {
-  const long long o = (long long)m * p.ldo + n;
-  if (vec) {
-    if (p.out_f32) {
-      f32x4* d = reinterpret_cast<f32x4*>(static_cast<float*>(p.out) + o);
-      d[0] = f32x4{v[0], v[1], v[2], v[3]};
-      d[1] = f32x4{v[4], v[5], v[6], v[7]};
-    } else {
-      bf16x8 w;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) w[e] = static_cast<bf16>(v[e]);
-      *reinterpret_cast<bf16x8*>(static_cast<bf16*>(p.out) + o) = w;
-    }
+
+// Register layout (lane: row l % 32) <-> store layout (lane: row l % 16, a later column group
+// in the odd 16-lane rows): a, b hold two column groups of 32 rows on one side, 16-row
+// halves of both groups on the other. Self-inverse.
+__device__ __forceinline__ void rows16(uint4& a, uint4& b) {
+  const Pair x = swap16(a.x, b.x), y = swap16(a.y, b.y), z = swap16(a.z, b.z), w = swap16(a.w, b.w);
+  a = make_uint4(x.a, y.a, z.a, w.a);
+  b = make_uint4(x.b, y.b, z.b, w.b);
+}
+__device__ __forceinline__ void rows16(f32x4& a, f32x4& b) {
+  uint4 u = __builtin_bit_cast(uint4, a), v = __builtin_bit_cast(uint4, b);
+  rows16(u, v);
+  a = __builtin_bit_cast(f32x4, u);
+  b = __builtin_bit_cast(f32x4, v);
+}
+
+// Two groups of four columns, v0 of g and v1 of g + 1 (g even) -> 8 consecutive columns of the
+// row in 16 bytes: columns 8 g .. in lanes 0 - 31, 8 g + 8 .. in lanes 32 - 63.
+__device__ __forceinline__ uint4 bf16_row8(const float* v0, const float* v1) {
+  const Pair x = swap32(pack_bf16(v0[0], v0[1]), pack_bf16(v1[0], v1[1]));
+  const Pair y = swap32(pack_bf16(v0[2], v0[3]), pack_bf16(v1[2], v1[3]));
+  return make_uint4(x.a, y.a, x.b, y.b);
+}
+
+__device__ __forceinline__ void add_bf16x4(float* v, unsigned lo, unsigned hi) {
+  v[0] += __uint_as_float(lo << 16);
+  v[1] += __uint_as_float(lo & 0xffff0000u);
+  v[2] += __uint_as_float(hi << 16);
+  v[3] += __uint_as_float(hi & 0xffff0000u);
+}
+
+// x * Phi(x) with Phi from the erf of Abramowitz & Stegun 7.1.26, as gelu_erf, arranged as
+// max(x, 0) - |x| q with q = (1 - erf(|x| / sqrt 2)) / 2 (halved coefficients): four VALU
+// operations fewer, and no cancellation for negative x.
+__device__ __forceinline__ float gelu_q(float x) {
+  const float ax = fabsf(x);
+  const float t = __builtin_amdgcn_rcpf(fmaf(ax, 0.3275911f * 0.70710678118654752f, 1.0f));
+  const float poly = t * (0.127414796f + t * (-0.142248368f + t * (0.7107068705f + t * (-0.7265760135f + t * 0.5307027145f))));
+  const float e = __builtin_amdgcn_exp2f(x * (x * -0.72134752044448170f));
+  return fmaf(-fminf(ax, 3.4e38f), poly * e, fmaxf(x, 0.0f));  // finite |x| times zero at x = +-inf
+}
+
+// Accumulators scaled by the column's weight scale (fp8) or as they are.
+template <bool SCALE> __device__ __forceinline__ f32x4 epi_scale(const GemmParams& p, int n) {
+  if constexpr (SCALE) return ld_f4(p.wscale + n);
+  return f32x4{1.f, 1.f, 1.f, 1.f};
+}
+
+// Four output columns [n, n + 4) of row m in the output type, masked past n_store.
+template <bool SCALE> __device__ __forceinline__ void store_out4(const GemmParams& p, int m, int n, const float* v) {
+  if (SCALE && p.out_fp8) {
+    uint8_t* o = static_cast<uint8_t*>(p.out) + (long long)m * p.ldo + n;
+    const unsigned w = fp8x4(v[0], v[1], v[2], v[3]);
+    for (int e = 0; e < 4; ++e)
+      if (n + e < p.n_store) o[e] = static_cast<uint8_t>(w >> (8 * e));
   } else {
     store4<bf16>(p, m, n, v, p.n_store);
-    store4<bf16>(p, m, n + 4, v + 4, p.n_store);
+  }
+}
+
+// One wave's 32 rows x 32 FN accumulator columns in LDS -> outputs, any layout.
+template <int FN, bool SCALE>
+__device__ __forceinline__ void generic_rows(const GemmParams& p, const float* ep, int mb, int nw0) {
+  constexpr int WN = 32 * FN, EPL = WN + 4;
+  const int lane = threadIdx.x & 63;
+  const int cols = p.geglu ? WN / 2 : WN;  // output columns of the wave
+#pragma unroll 1
+  for (int t = lane; t < 32 * (cols / 4); t += 64) {
+    const int rr = t / (cols / 4), c = (t - rr * (cols / 4)) * 4;
+    const int m = mb + rr;
+    if (m >= p.M) continue;
+    float v[4];
+    if (p.geglu) {
+      const int lc = c / 32 * 64 + c % 32;  // value column; its gate is 32 further
+      const int o = nw0 / 2 + c, nv = nw0 + lc;
+      if (o >= p.n_store) continue;
+      for (int e = 0; e < 4; ++e) {
+        float a = ep[rr * EPL + lc + e], g = ep[rr * EPL + lc + 32 + e];
+        if constexpr (SCALE) a *= p.wscale[nv + e], g *= p.wscale[nv + 32 + e];
+        if (p.bias) a += p.bias[nv + e], g += p.bias[nv + 32 + e];
+        v[e] = a * gelu_q(g);
+      }
+      store_out4<SCALE>(p, m, o, v);
+    } else {
+      const int n = nw0 + c;
+      for (int e = 0; e < 4; ++e) {
+        v[e] = ep[rr * EPL + c + e];
+        if constexpr (SCALE) v[e] *= n + e < p.n_store ? p.wscale[n + e] : 0.f;
+      }
+      if (SCALE && p.out_fp8) {
+        for (int e = 0; e < 4; ++e) {
+          if (n + e >= p.n_store) continue;
+          if (p.bias) v[e] += p.bias[n + e];
+          const long long ro = (long long)m * p.ldr + n + e;
+          if (p.resid)
+            v[e] += p.resid_f32 ? static_cast<const float*>(p.resid)[ro]
+                                : static_cast<float>(static_cast<const bf16*>(p.resid)[ro]);
+        }
+        store_out4<SCALE>(p, m, n, v);
+      } else {
+        epilogue_group<bf16>(p, m, n, v);
+      }
+    }
+  }
+}
+
+// The wave's blocks acc[i][j] (rows m0 + 32 i .., columns nw0 + 32 j ..), i < FM, j < FN.
+// pin: with use_pin, the fp32 residual of the kEpiF32 kind already in registers.
+// ep: 32 x (32 FN + 4) floats of LDS of this wave (generic path).
+template <int FM, int FN, bool SPLIT, bool SCALE, bool PIN>
+__device__ __forceinline__ void wave_epilogue(const GemmParams& p, const f32x16 (*acc)[FN], const int m0, const int nw0,
+                                              const int split, const int kind, const f32x4 (*pin)[FN][4], const bool use_pin,
+                                              float* ep) {
+  const int lane = threadIdx.x & 63;
+  const int row = lane & 31, hh = lane >> 5, h4 = 4 * hh;
+  // store layout: row and, for fp32 (a pair of g) and bf16 (a 32-column block), first column
+  const int r16 = lane & 15, c8 = 8 * ((lane >> 4) & 1) + h4, c16 = 16 * ((lane >> 4) & 1) + 8 * hh;
+  if constexpr (SPLIT) {
+    // whole rows of the wave's columns through LDS (128 or 256 bytes per row and store): the
+    // slabs are the largest output here, and 64-byte pieces straight from registers took
+    // 49.5 us instead of 45.3 (2048 x 1280 x 5120, four slabs)
+    constexpr int WN = 32 * FN, EPL = WN + 4, LPR = WN / 4, RPI = 64 / LPR;
+    float* slab = p.part + (long long)split * p.M * p.n_store;
+    const int c4 = (lane % LPR) * 4, n = nw0 + c4;
+    f32x4 sc = {1.f, 1.f, 1.f, 1.f};
+    if constexpr (SCALE) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) sc[e] = n + e < p.n_store ? p.wscale[n + e] : 0.f;
+    }
+#pragma unroll
+    for (int i = 0; i < FM; ++i) {
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+          *reinterpret_cast<f32x4*>(ep + row * EPL + j * 32 + 8 * g + h4) =
+              f32x4{acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
+#pragma unroll
+      for (int t = 0; t < 32 / RPI; ++t) {
+        const int rr = t * RPI + lane / LPR, m = m0 + 32 * i + rr;
+        f32x4 v = *reinterpret_cast<const f32x4*>(ep + rr * EPL + c4);
+        if (m >= p.M || n >= p.n_store) continue;
+        if constexpr (SCALE) v *= sc;
+        *reinterpret_cast<f32x4*>(slab + (long long)m * p.n_store + n) = v;
+      }
+    }
+    return;
+  }
+  // value of register 4 g + e with the column scale and the bias
+  auto biased = [&](const f32x16& a, int n, int g, const f32x4& bias, float* v) {
+    const f32x4 sc = epi_scale<SCALE>(p, n + 8 * g + h4);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = (SCALE ? a[4 * g + e] * sc[e] : a[4 * g + e]) + bias[e];
+  };
+  // a bf16 block of 32 rows and columns [n, n + 32), as bf16_row8 gives it
+  auto store_rows = [&](int mb, int n, uint4 w0, uint4 w1) {
+    rows16(w0, w1);
+    bf16* d = static_cast<bf16*>(p.out) + (long long)(mb + r16) * p.ldo + n + c16;
+    if (mb + r16 < p.M) *reinterpret_cast<uint4*>(d) = w0;
+    if (mb + r16 + 16 < p.M) *reinterpret_cast<uint4*>(d + 16ll * p.ldo) = w1;
+  };
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  if (kind == kEpiGeglu) {
+    if constexpr (FN % 2 == 0) {
+#pragma unroll
+      for (int j = 0; j < FN; j += 2) {
+        const int n = nw0 + 32 * j, o = n / 2;  // value columns n .. n + 31, gates n + 32 ..
+        if (o >= p.n_store) break;
+        f32x4 ba[4], bg[4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          ba[g] = p.bias ? ld_f4(p.bias + n + 8 * g + h4) : zero;
+          bg[g] = p.bias ? ld_f4(p.bias + n + 32 + 8 * g + h4) : zero;
+        }
+#pragma unroll
+        for (int i = 0; i < FM; ++i) {
+          const int m = m0 + 32 * i + row;
+          float v[4][4];
+#pragma unroll
+          for (int g = 0; g < 4; ++g) {
+            float va[4], vg[4];
+            biased(acc[i][j], n, g, ba[g], va);
+            biased(acc[i][j + 1], n + 32, g, bg[g], vg);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[g][e] = va[e] * gelu_q(vg[e]);
+          }
+          if (SCALE && p.out_fp8) {
+            // 4 codes per g; two swaps give a lane 16 consecutive codes of 32
+            const Pair x = swap32(fp8x4(v[0][0], v[0][1], v[0][2], v[0][3]), fp8x4(v[2][0], v[2][1], v[2][2], v[2][3]));
+            const Pair y = swap32(fp8x4(v[1][0], v[1][1], v[1][2], v[1][3]), fp8x4(v[3][0], v[3][1], v[3][2], v[3][3]));
+            if (m < p.M)
+              *reinterpret_cast<uint4*>(static_cast<uint8_t*>(p.out) + (long long)m * p.ldo + o + 16 * hh) = make_uint4(x.a, x.b, y.a, y.b);
+          } else {
+            store_rows(m0 + 32 * i, o, bf16_row8(v[0], v[1]), bf16_row8(v[2], v[3]));
+          }
+        }
+      }
+    }
+    return;
+  }
+  if (kind == kEpiF32) {
+    // residual of block t = i FN + j (fp32, or bf16 widened when it is used), one block ahead
+    f32x4 rf[2][4];
+    bf16x4 rb[2][4];
+    const bool rf32 = p.resid && p.resid_f32 && !(PIN && use_pin), rb16 = p.resid && !p.resid_f32;
+    auto load_resid = [&](int t) {
+      const int n = min(nw0 + 32 * (t % FN), p.n_store - 32), mb = m0 + 32 * (t / FN);
+      if (rf32) {  // store layout: rf[g], rf[g + 1] the two 16-row halves of the pair
+        const float* r0 = static_cast<const float*>(p.resid) + (long long)min(mb + r16, p.M - 1) * p.ldr + n + c8;
+        const float* r1 = static_cast<const float*>(p.resid) + (long long)min(mb + r16 + 16, p.M - 1) * p.ldr + n + c8;
+#pragma unroll
+        for (int g = 0; g < 4; g += 2) {
+          rf[t & 1][g] = ld_f4(r0 + 8 * g);
+          rf[t & 1][g + 1] = ld_f4(r1 + 8 * g);
+        }
+      }
+      if (rb16) {
+        const bf16* r = static_cast<const bf16*>(p.resid) + (long long)min(mb + row, p.M - 1) * p.ldr + n + h4;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) rb[t & 1][g] = *reinterpret_cast<const bf16x4*>(r + 8 * g);
+      }
+    };
+    load_resid(0);
+    f32x4 bias[FN][4];
+#pragma unroll
+    for (int j = 0; j < FN; ++j)
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        bias[j][g] = p.bias ? ld_f4(p.bias + min(nw0 + 32 * j, p.n_store - 32) + 8 * g + h4) : zero;
+#pragma unroll
+    for (int i = 0; i < FM; ++i) {
+      const int m = m0 + 32 * i + row;
+      const float* rv = p.rowvec ? p.rowvec + (long long)(min(m, p.M - 1) / p.rows_per_sample) * p.rowvec_ld + h4 : nullptr;
+#pragma unroll
+      for (int j = 0; j < FN; ++j) {
+        const int n = nw0 + 32 * j, t = i * FN + j;
+        if (t + 1 < FM * FN) load_resid(t + 1);
+        if (n >= p.n_store) continue;
+        f32x4 w[4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          float v[4];
+          biased(acc[i][j], n, g, bias[j][g], v);
+          w[g] = f32x4{v[0], v[1], v[2], v[3]};
+          if (rv) w[g] += ld_f4(rv + n + 8 * g);
+          if (rb16)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) w[g][e] += static_cast<float>(rb[t & 1][g][e]);
+        }
+#pragma unroll
+        for (int g = 0; g < 4; g += 2) {
+          rows16(w[g], w[g + 1]);
+          if constexpr (PIN) {
+            if (use_pin) {
+              w[g] += pin[i][j][g];
+              w[g + 1] += pin[i][j][g + 1];
+            }
+          }
+          if (rf32) {
+            w[g] += rf[t & 1][g];
+            w[g + 1] += rf[t & 1][g + 1];
+          }
+          float* d = static_cast<float*>(p.out) + (long long)(m0 + 32 * i + r16) * p.ldo + n + 8 * g + c8;
+          if (m0 + 32 * i + r16 < p.M) *reinterpret_cast<f32x4*>(d) = w[g];
+          if (m0 + 32 * i + r16 + 16 < p.M) *reinterpret_cast<f32x4*>(d + 16ll * p.ldo) = w[g + 1];
+        }
+      }
+    }
+    return;
+  }
+  if (kind == kEpiBf16) {
+    // residual: bf16 as whole 16-byte rows, one block t = i FN + j ahead (swapped into the
+    // register layout when used), or fp32
+    uint4 rb[2][2];
+    const bool rb16 = p.resid && !p.resid_f32, rf32 = p.resid && p.resid_f32;
+    auto load_resid = [&](int t) {
+      if (!rb16) return;
+      const int mb = m0 + 32 * (t / FN);
+      const bf16* r = static_cast<const bf16*>(p.resid) + min(nw0 + 32 * (t % FN), p.n_store - 32) + c16;
+      rb[t & 1][0] = *reinterpret_cast<const uint4*>(r + (long long)min(mb + r16, p.M - 1) * p.ldr);
+      rb[t & 1][1] = *reinterpret_cast<const uint4*>(r + (long long)min(mb + r16 + 16, p.M - 1) * p.ldr);
+    };
+    load_resid(0);
+    f32x4 bias[FN][4];
+#pragma unroll
+    for (int j = 0; j < FN; ++j)
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        bias[j][g] = p.bias ? ld_f4(p.bias + min(nw0 + 32 * j, p.n_store - 32) + 8 * g + h4) : zero;
+#pragma unroll
+    for (int i = 0; i < FM; ++i) {
+      const int m = m0 + 32 * i + row;
+      const float* rv = p.rowvec ? p.rowvec + (long long)(min(m, p.M - 1) / p.rows_per_sample) * p.rowvec_ld + h4 : nullptr;
+      const float* rf =
+          rf32 ? static_cast<const float*>(p.resid) + (long long)min(m, p.M - 1) * p.ldr + h4 : nullptr;
+      // V^T output: sample and token of the row
+      int vb = 0, vs = 0;
+      if (p.vt && nw0 + 32 * FN > p.vt_col0) {
+        vb = m / p.vt_seq;
+        vs = m - vb * p.vt_seq;
+      }
+#pragma unroll
+      for (int j = 0; j < FN; ++j) {
+        const int n = nw0 + 32 * j, tb = i * FN + j;
+        if (tb + 1 < FM * FN) load_resid(tb + 1);
+        if (n >= p.n_store) continue;
+        float v[4][4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) biased(acc[i][j], n, g, bias[j][g], v[g]);
+        if (p.vt && n >= p.vt_col0) {
+          // rows are tokens: neighbouring lanes exchange one of two columns, so a lane
+          // stores two consecutive tokens of a column (4 bytes; 64-byte segments)
+          const int nn = n - p.vt_col0, h = nn / p.vt_dp, d = nn - h * p.vt_dp;
+          const bool odd = lane & 1;
+          bf16* dst = static_cast<bf16*>(p.vt) +
+                      (((long long)vb * p.vt_heads + h) * p.vt_dp + d + h4 + (odd ? 1 : 0)) * p.vt_ld + (vs & ~1);
+          const unsigned sel = odd ? 0x03020706u : 0x05040100u;
+#pragma unroll
+          for (int g = 0; g < 4; ++g)
+#pragma unroll
+            for (int e = 0; e < 4; e += 2) {
+              const unsigned x = pack_bf16(v[g][e], v[g][e + 1]);
+              const unsigned y = __builtin_amdgcn_update_dpp(0u, x, 0xb1, 0xf, 0xf, true);  // lane ^ 1
+              const unsigned w = __builtin_amdgcn_perm(y, x, sel);
+              if (m < p.M) *reinterpret_cast<unsigned*>(dst + (long long)(8 * g + e) * p.vt_ld) = w;
+            }
+          continue;
+        }
+        if (rv)
+#pragma unroll
+          for (int g = 0; g < 4; ++g) {
+            const f32x4 r = ld_f4(rv + n + 8 * g);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[g][e] += r[e];
+          }
+        if (rf)
+#pragma unroll
+          for (int g = 0; g < 4; ++g) {
+            const f32x4 r = ld_f4(rf + n + 8 * g);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[g][e] += r[e];
+          }
+        if (rb16) {
+          rows16(rb[tb & 1][0], rb[tb & 1][1]);
+#pragma unroll
+          for (int t = 0; t < 2; ++t) {
+            const uint4 r = rb[tb & 1][t];
+            const Pair x = swap32(r.x, r.z), y = swap32(r.y, r.w);
+            add_bf16x4(v[2 * t], x.a, y.a);
+            add_bf16x4(v[2 * t + 1], x.b, y.b);
+          }
+        }
+        store_rows(m0 + 32 * i, n, bf16_row8(v[0], v[1]), bf16_row8(v[2], v[3]));
+      }
+    }
+    return;
+  }
+  // generic: 32 rows at a time through LDS, one group of four columns per lane and step
+  constexpr int WN = 32 * FN, EPL = WN + 4;
+#pragma unroll
+  for (int i = 0; i < FM; ++i) {
+#pragma unroll
+    for (int j = 0; j < FN; ++j)
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        *reinterpret_cast<f32x4*>(ep + row * EPL + j * 32 + 8 * g + h4) =
+            f32x4{acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
+    generic_rows<FN, SCALE>(p, ep, m0 + 32 * i, nw0);
   }
 }
 
@@ -154,26 +526,23 @@ template <int BM, int FN, int S, int NW, bool X5 = false> constexpr size_t frag_
 // 2 implicit 3x3 convolution (one source). SPLIT: write fp32 partial tiles.
 // D: B register buffers (B is loaded D stages ahead). WPE: waves per SIMD the register
 // allocation must allow (2: two workgroups share a CU, so one's prologue, barriers and
-// epilogue overlap the other's MFMAs). PRE: read a whole LDS stage of A fragments one
-// stage ahead into registers (small tiles, whose few MFMAs per k-step cannot cover an
-// LDS read latency), instead of one k-step ahead. NW: waves per workgroup, each owning
+// epilogue overlap the other's MFMAs). NW: waves per workgroup, each owning
 // 32 FN columns; with five (a 160-column tile) the first four issue the A DMA. X5: the
 // 160-column tile on four waves (see the file comment).
 // One unit: the BM x BN tile at (m0, n0) over the K stages [kt0, kt1) (split-K part
 // `split` when SPLIT).
-template <int BM, int FN, int S, int D, int WPE, int MODE, bool SPLIT, int PRE, int NW, bool X5>
+template <int BM, int FN, int S, int D, int WPE, int MODE, bool SPLIT, int NW, bool X5>
 __device__ __forceinline__ void frag_tile(const GemmParams& p, const int m0, const int n0, const int split,
                                           const int kt0, const int kt1) {
   constexpr int FM = BM / 32;
   constexpr int WN = 32 * FN;
-  constexpr int BN = X5 ? 160 : NW * WN;
-  static_assert(!X5 || (NW == 4 && FN == 1 && !PRE), "X5: four waves of one column block each");
+  static_assert(!X5 || (NW == 4 && FN == 1), "X5: four waves of one column block each");
   constexpr int NB = 4 * FN + (X5 ? 1 : 0);  // B loads per wave and stage
   constexpr int STAGE = BM * kRowBytes;
   constexpr int PW = BM / 32;  // DMA instructions (8 rows of 128 B) per DMA wave per stage
   static_assert(NW == 4 || NW == 5, "four or five waves");
   constexpr int NM = FM * FN;
-  static_assert(D >= 1 && D <= 3 && (!PRE || D <= 2), "one to three B buffers (two with read-ahead)");
+  static_assert(D >= 1 && D <= 3, "one to three B buffers");
   static_assert(S >= 2 && S <= 6, "2 to 6 LDS stages");
   static_assert(BM % 32 == 0 && BM <= 256, "BM");
 
@@ -303,41 +672,32 @@ __device__ __forceinline__ void frag_tile(const GemmParams& p, const int m0, con
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc5[i][r] = 0.f;
 
-  // Epilogue input of the plain path (the residual or the per-sample row vector, when
-  // exactly one is present) for small wave tiles of the linear modes without stage
-  // read-ahead (where the registers are free): loaded into FM x ENP x 2 16-byte registers
-  // per lane, in the layout of the row-contiguous epilogue (8 consecutive columns per
-  // lane). The loads are issued right after the prologue's A and B loads, so the first
-  // wait (in-order vector-memory counter) does not include them and the main loop's
-  // latency hides them.
-  constexpr int ELPR = WN / 8;     // lanes per row in the row-contiguous epilogue
-  constexpr int ERPI = 64 / ELPR;  // rows per pass
-  constexpr int ENP = 32 / ERPI;   // passes per 32-row block
-  constexpr bool kPreIn = !SPLIT && !PRE && MODE != 2 && FM * ENP * 8 <= 32 && WPE <= 2;
-  const int enw0 = n0 + wave * WN;
-  const bool pre_in = kPreIn && !p.geglu && !(p.vt && enw0 + WN > p.vt_col0) &&
-                      ((p.resid != nullptr) != (p.rowvec != nullptr));
-  f32x4 pin[kPreIn ? FM : 1][kPreIn ? ENP : 1][2];
+  // fp32 residual of an fp32 output for small wave tiles of the linear modes (where the
+  // registers are free): loaded right after the prologue's A and B loads, so the first wait
+  // (in-order vector-memory counter) does not include it and the main loop hides it.
+  const int kind = SPLIT ? 0 : epi_kind(p);
+  constexpr bool kPreIn = !SPLIT && !X5 && MODE != 2 && FM * FN <= 2 && WPE <= 2;
+  const int nw0 = n0 + wave * WN;
+  const bool pre_in = kPreIn && kind == kEpiF32 && p.resid && p.resid_f32;
+  f32x4 pin[kPreIn ? FM : 1][FN][4];
   auto load_pre_in = [&]() {
     if constexpr (kPreIn) {
       if (pre_in) {
-        const int n = enw0 + (lane % ELPR) * 8;
-        const bool rvec = n + 8 <= p.n_store && p.resid && resid_vec8(p);
 #pragma unroll
-        for (int i = 0; i < FM; ++i)
+        for (int i = 0; i < FM; ++i) {
+          // store layout of wave_epilogue: 16-row halves of each pair of g
+          const float* r = static_cast<const float*>(p.resid) + 8 * ((lane >> 4) & 1) + 4 * (lane >> 5);
+          const float* r0 = r + (long long)min(m0 + i * 32 + (lane & 15), p.M - 1) * p.ldr;
+          const float* r1 = r + (long long)min(m0 + i * 32 + 16 + (lane & 15), p.M - 1) * p.ldr;
 #pragma unroll
-          for (int t = 0; t < ENP; ++t) {
-            const int m = m0 + i * 32 + t * ERPI + lane / ELPR;
-            float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-            if (m < p.M && n < p.n_store) {
-              if (p.rowvec)
-                load_rowvec8(p, m, n, v);
-              else
-                load_resid8(p, m, n, rvec, v);
+          for (int j = 0; j < FN; ++j)
+#pragma unroll
+            for (int g = 0; g < 4; g += 2) {
+              const int n = min(nw0 + 32 * j, p.n_store - 32) + 8 * g;
+              pin[i][j][g] = ld_f4(r0 + n);
+              pin[i][j][g + 1] = ld_f4(r1 + n);
             }
-            pin[i][t][0] = f32x4{v[0], v[1], v[2], v[3]};
-            pin[i][t][1] = f32x4{v[4], v[5], v[6], v[7]};
-          }
+        }
       }
     }
   };
@@ -366,61 +726,7 @@ __device__ __forceinline__ void frag_tile(const GemmParams& p, const int m0, con
     for (int i = 0; i < FM; ++i) acc5[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, a5[i], acc5[i], 0, 0, 0);
   };
 
-  BReg bq[D];
-  if constexpr (PRE) {
-    // Stage kt: hand-over first (this wave's DMA of stage kt + 1 landed: at most VM_PRE
-    // later VM loads pending; after the barrier every wave's has, and every wave is done
-    // with the slot of stage kt - 1, whose fragments it read a stage earlier and used),
-    // then the DMA of stage kt + S - 1 into that slot, the reads of all of stage kt + 1's
-    // fragments into the other register set, and stage kt's MFMAs from registers with the
-    // B loads of stage kt + D as B registers free up.
-    // VM loads after the DMA of stage kt + 1 (issued at the start of stage kt + 2 - S):
-    // 4 FN B loads of that stage, then S - 3 stages of PW DMA + 4 FN B loads. When that DMA
-    // came from the prologue (kt = kt0 + r, r <= S - 2; stage kt0 issues no DMA) the count
-    // is (S - 3) PW + 4 D FN + 4 r FN, enough once D + r >= S - 2; r = 0 is the prologue wait.
-    static_assert(S == 3 || (S == 4 && D >= 1), "stage read-ahead: 3 or 4 LDS stages");
-    constexpr int VM_PRE = 4 * FN + (S - 3) * (PW + 4 * FN);
-    static_assert(VM_PRE < 64 && (S - 2) * PW + D * 4 * FN < 64, "vmcnt range");
-    typedef bf16x8 AStage[4][FM];
-    AStage sa[2];
-    auto read_stage = [&](int slot, AStage& dst) {
-#pragma unroll
-      for (int s = 0; s < 4; ++s) read_a(slot, s, dst[s]);
-    };
-#pragma unroll
-    for (int s = 0; s < S; ++s) issue_a(kt0 + s, s);
-#pragma unroll
-    for (int d = 0; d < D; ++d)
-#pragma unroll
-      for (int s = 0; s < 4; ++s) load_b_step(kt0 + d, s, bq[d]);
-    __builtin_amdgcn_s_waitcnt(wait_vm_lgkm0((S - 2) * PW + D * 4 * FN));
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_sched_barrier(0);
-    read_stage(0, sa[0]);
-    auto pstage = [&](int kt, AStage& cur, AStage& nxt, BReg& bb) {
-      const int r = kt - kt0;
-      __builtin_amdgcn_s_waitcnt(wait_vm_lgkm0(VM_PRE));
-      __builtin_amdgcn_s_barrier();
-      __builtin_amdgcn_sched_barrier(0);
-      if (r >= 1) issue_a(kt + S - 1, (r - 1) % S);
-      read_stage((r + 1) % S, nxt);
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        mfmas(cur[s], bb[s]);
-        load_b_step(kt + D, s, bb);
-      }
-      KSched<0, 4 * NM, 4 * FM, 4 * FN>::apply();
-      __builtin_amdgcn_sched_barrier(0);
-    };
-    // Pairs of stages, then the odd one: no stage of the loop body is conditional, so the
-    // compiler's wait for a B register counts both stages' loads issued after it.
-    int kt = kt0;
-    for (; kt + 1 < kt1; kt += 2) {
-      pstage(kt, sa[0], sa[1], bq[0]);
-      pstage(kt + 1, sa[1], sa[0], bq[D - 1]);
-    }
-    if (kt < kt1) pstage(kt, sa[0], sa[1], bq[0]);
-  } else {
+  {
     BReg bq[D];
     bf16x8 b5q[X5 ? D : 1];
     // One k-step: [the DMA of a later A stage first, when `dma`], the next k-step's A
@@ -519,186 +825,34 @@ __device__ __forceinline__ void frag_tile(const GemmParams& p, const int m0, con
   __builtin_amdgcn_s_waitcnt(wait_vm_lgkm0(0));
   __syncthreads();
 
-  // ---- epilogue
-  const int col = lane & 31;
-  const int h4 = 4 * (lane >> 5);
-  const int nw0 = n0 + wave * WN;
-  // X5: the partial sums of column block 4 go to LDS in the register layout; wave w < FM
-  // then sums row block w of it over the four waves in wave order.
-  f32x16 acc5t;
+  // ---- epilogue (one wave-private LDS block for the generic path)
+  float* ep = reinterpret_cast<float*>(smem) + wave * (32 * (WN + 4));
   if constexpr (X5) {
+    // the partial sums of column block 4 go to LDS in the register layout; wave w < FM then
+    // sums row block w of it over the four waves in wave order
     float* part5 = reinterpret_cast<float*>(smem);
 #pragma unroll
     for (int i = 0; i < FM; ++i)
 #pragma unroll
       for (int r = 0; r < 16; ++r) part5[((wave * FM + i) * 16 + r) * 64 + lane] = acc5[i][r];
     __syncthreads();
+    f32x16 blk5[1][1];
     if (wave < FM) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc5t[r] = part5[((0 * FM + wave) * 16 + r) * 64 + lane];
+      for (int r = 0; r < 16; ++r) blk5[0][0][r] = part5[((0 * FM + wave) * 16 + r) * 64 + lane];
 #pragma unroll
       for (int w = 1; w < 4; ++w)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc5t[r] += part5[((w * FM + wave) * 16 + r) * 64 + lane];
+        for (int r = 0; r < 16; ++r) blk5[0][0][r] += part5[((w * FM + wave) * 16 + r) * 64 + lane];
     }
     __syncthreads();
-  }
-  if (!X5 && !SPLIT && p.vt && nw0 + WN > p.vt_col0) {
-    // columns of the per-head V^T output (or a wave straddling it): register layout,
-    // lanes 0..31 = 32 consecutive tokens of one column
-#pragma unroll
-    for (int i = 0; i < FM; ++i) {
-      const int m = m0 + i * 32 + col;
-      if (m >= p.M) continue;
-#pragma unroll
-      for (int j = 0; j < FN; ++j)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const int n = nw0 + j * 32 + 8 * g + h4;
-          float v[4] = {acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
-          epilogue_group<bf16>(p, m, n, v);
-        }
-    }
-    return;
-  }
-  // Row-contiguous phase: 32 rows x WN fp32 per wave in LDS (row pitch WN + 4 floats:
-  // the 16-byte writes of rows r .. r + 7 fall on distinct banks).
-  constexpr int EPL = WN + 4;
-  float* ep = reinterpret_cast<float*>(smem) + wave * (32 * EPL);
-  float* slab = SPLIT ? p.part + (long long)split * p.M * p.n_store : nullptr;
-  // One 32-row block of this wave's columns [nw0, nw0 + WN): blk[j] the accumulators of
-  // column block j, rows mb .. mb + 31; i < 0: no preloaded epilogue input (the extra
-  // column-block-4 block of X5), else its row block.
-  auto epi_block = [&](const f32x16* blk, const int mb, const int nw0, const int i) {
-    const bool pre_in_b = pre_in && i >= 0;
-    const int ip = i >= 0 ? i : 0;
-#pragma unroll
-    for (int j = 0; j < FN; ++j)
-#pragma unroll
-      for (int g = 0; g < 4; ++g)
-        *reinterpret_cast<f32x4*>(ep + col * EPL + j * 32 + 8 * g + h4) =
-            f32x4{blk[j][4 * g], blk[j][4 * g + 1], blk[j][4 * g + 2], blk[j][4 * g + 3]};
-    if (SPLIT) {
-      constexpr int LPR = WN / 4;   // lanes per row
-      constexpr int RPI = 64 / LPR; // rows per pass
-#pragma unroll
-      for (int t = 0; t < 32 / RPI; ++t) {
-        const int rr = t * RPI + lane / LPR;
-        const int c4 = (lane % LPR) * 4;
-        const f32x4 v4 = *reinterpret_cast<const f32x4*>(ep + rr * EPL + c4);
-        const int m = mb + rr, n = nw0 + c4;
-        if (m >= p.M || n >= p.n_store) continue;
-        *reinterpret_cast<f32x4*>(slab + (long long)m * p.n_store + n) = v4;
-      }
-    } else if (!p.geglu) {
-      // A lane takes 8 consecutive columns of a row (16-byte bf16 stores: 4 lanes cover
-      // a row's 64-byte segment), the same in every pass; the row vector and residual of
-      // every pass of this 32-row block are loaded before the block is read back from
-      // LDS, so the block waits on one memory latency instead of one per pass. Same
-      // arithmetic as epilogue_group: ((acc + bias) + row vector) + residual.
-      constexpr int LPR = WN / 8;
-      constexpr int RPI = 64 / LPR;
-      constexpr int NP = 32 / RPI;
-      const int c8 = (lane % LPR) * 8;
-      const int n = nw0 + c8;
-      const bool ncol = n < p.n_store;
-      const bool full = n + 8 <= p.n_store;
-      const bool rvec = full && p.resid && resid_vec8(p);
-      float rv[NP][8], rs[NP][8];
-#pragma unroll
-      for (int t = 0; t < NP; ++t) {
-        const int m = mb + t * RPI + lane / LPR;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) rv[t][e] = rs[t][e] = 0.f;
-        if (m >= p.M || !ncol || pre_in_b) continue;
-        if (p.rowvec) load_rowvec8(p, m, n, rv[t]);
-        if (p.resid) load_resid8(p, m, n, rvec, rs[t]);
-      }
-      float bias8[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) bias8[e] = p.bias && n + e < p.n_store ? p.bias[n + e] : 0.f;
-      const bool ovec = full && out_vec8(p);
-#pragma unroll
-      for (int t = 0; t < NP; ++t) {
-        const int rr = t * RPI + lane / LPR;
-        const f32x4 a0 = *reinterpret_cast<const f32x4*>(ep + rr * EPL + c8);
-        const f32x4 a1 = *reinterpret_cast<const f32x4*>(ep + rr * EPL + c8 + 4);
-        const int m = mb + rr;
-        if (m >= p.M || !ncol) continue;
-        float v[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          float x = e < 4 ? a0[e] : a1[e - 4];
-          if (p.bias) x += bias8[e];
-          if constexpr (kPreIn) {
-            if (pre_in_b) x += pin[ip][t][e / 4][e % 4];
-          }
-          if (!pre_in_b) {
-            if (p.rowvec) x += rv[t][e];
-            if (p.resid) x += rs[t][e];
-          }
-          v[e] = x;
-        }
-        store8(p, m, n, v, ovec);
-      }
-    } else {
-      // GEGLU: within each 64-column pair block, columns [0, 32) are values and
-      // [32, 64) the matching gates; output column = (pair block) * 32 + c. A lane takes
-      // 8 consecutive outputs of a row, so each store is 16 bytes (4 lanes cover a row's
-      // 64-byte segment); its value and gate columns are the same in every pass, so
-      // their biases load once.
-      // (tiles with 32 columns per wave never take GEGLU: the host rejects them)
-      if constexpr (WN % 64 == 0) {
-        constexpr int LPR = WN / 16;
-        constexpr int RPI = 64 / LPR;
-        const int cq = (lane % LPR) * 8;            // 0 .. WN/2 - 8
-        const int pb = cq / 32, c8 = cq % 32;       // pair block, column in it
-        const int lc = pb * 64 + c8;                // value column within the wave
-        const int nv = nw0 + lc;
-        const int o = nw0 / 2 + cq;
-        float ba[8], bg[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) ba[e] = bg[e] = 0.f;
-        if (p.bias && o < p.n_store) {
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            ba[e] = p.bias[nv + e];
-            bg[e] = p.bias[nv + 32 + e];
-          }
-        }
-        const bool vec8 = !p.out_f32 && o + 8 <= p.n_store && out_vec8(p);
-#pragma unroll
-        for (int t = 0; t < 32 / RPI; ++t) {
-          const int rr = t * RPI + lane / LPR;
-          const f32x4 a0 = *reinterpret_cast<const f32x4*>(ep + rr * EPL + lc);
-          const f32x4 a1 = *reinterpret_cast<const f32x4*>(ep + rr * EPL + lc + 4);
-          const f32x4 g0 = *reinterpret_cast<const f32x4*>(ep + rr * EPL + lc + 32);
-          const f32x4 g1 = *reinterpret_cast<const f32x4*>(ep + rr * EPL + lc + 36);
-          const int m = mb + rr;
-          if (m >= p.M || o >= p.n_store) continue;
-          float v[8];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            v[e] = (a0[e] + ba[e]) * gelu_erf(g0[e] + bg[e]);
-            v[e + 4] = (a1[e] + ba[e + 4]) * gelu_erf(g1[e] + bg[e + 4]);
-          }
-          if (vec8) {
-            bf16x8 w;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) w[e] = static_cast<bf16>(v[e]);
-            *reinterpret_cast<bf16x8*>(static_cast<bf16*>(p.out) + (long long)m * p.ldo + o) = w;
-          } else {
-            store4<bf16>(p, m, o, v, p.n_store);
-            store4<bf16>(p, m, o + 4, v + 4, p.n_store);
-          }
-        }
-      }
-    }
-  };
-#pragma unroll
-  for (int i = 0; i < FM; ++i) epi_block(acc[i], m0 + i * 32, nw0, i);
-  if constexpr (X5) {
-    if (wave < FM) epi_block(&acc5t, m0 + wave * 32, n0 + 128, -1);
+    wave_epilogue<FM, FN, SPLIT, false, false>(p, acc, m0, nw0, split, kind, nullptr, false, ep);
+    if (wave < FM && n0 + 128 < p.N)
+      wave_epilogue<1, 1, SPLIT, false, false>(p, blk5, m0 + wave * 32, n0 + 128, split, kind, nullptr, false, ep);
+  } else if constexpr (kPreIn) {
+    wave_epilogue<FM, FN, SPLIT, false, true>(p, acc, m0, nw0, split, kind, pin, pre_in, ep);
+  } else {
+    wave_epilogue<FM, FN, SPLIT, false, false>(p, acc, m0, nw0, split, kind, nullptr, false, ep);
   }
 }
 
@@ -709,7 +863,7 @@ __device__ __forceinline__ void frag_tile(const GemmParams& p, const int m0, con
 // are multiples of the XCD count). A grid of BM-row tiles that fills a whole number of
 // rounds plus a fraction of one leaves that fraction to half the CUs; TBM-row tiles
 // spread it over all of them.
-template <int BM, int FN, int S, int D, int WPE, int MODE, bool SPLIT, int PRE, int NW = 4, bool X5 = false,
+template <int BM, int FN, int S, int D, int WPE, int MODE, bool SPLIT, int NW = 4, bool X5 = false,
           int TBM = 0>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE, WPE))) void gemm_frag_kernel(
     GemmParams p, int mt, int nt, int nsplit, int tail_full, int tail_bands) {
@@ -725,10 +879,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE, WP
       const int tx = tm * tail_bands / kXcds;
       if (idx < fx) {
         const int f = xcd * fx + idx;
-        frag_tile<BM, FN, S, D, WPE, MODE, SPLIT, PRE, NW, X5>(p, (f % mt) * BM, (f / mt) * BN, 0, 0, nk);
+        frag_tile<BM, FN, S, D, WPE, MODE, SPLIT, NW, X5>(p, (f % mt) * BM, (f / mt) * BN, 0, 0, nk);
       } else {
         const int t = xcd * tx + (idx - fx);
-        frag_tile<TBM, FN, S, 1, WPE, MODE, SPLIT, PRE, NW, X5>(p, (t % tm) * TBM,
+        frag_tile<TBM, FN, S, 1, WPE, MODE, SPLIT, NW, X5>(p, (t % tm) * TBM,
                                                                 (nt - tail_bands + t / tm) * BN, 0, 0, nk);
       }
       return;
@@ -743,7 +897,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(WPE, WP
   const int n_tile = ns / nsplit;
   const int kt0 = (int)((long long)split * nk / nsplit);
   const int kt1 = (int)((long long)(split + 1) * nk / nsplit);
-  frag_tile<BM, FN, S, D, WPE, MODE, SPLIT, PRE, NW, X5>(p, m_tile * BM, n_tile * BN, split, kt0, kt1);
+  frag_tile<BM, FN, S, D, WPE, MODE, SPLIT, NW, X5>(p, m_tile * BM, n_tile * BN, split, kt0, kt1);
 }
 
 // Sum of the split-K partial slabs [NS][M][n_store] in split order, then the epilogue;
@@ -787,7 +941,7 @@ void splitk_reduce(const GemmParams& p, int nsplit, hipStream_t s) {
   DN_HIP(hipGetLastError());
 }
 
-template <int BM, int FN, int S, int D, int WPE, int MODE, bool SPLIT, int PRE, int NW, bool X5, int TBM = 0>
+template <int BM, int FN, int S, int D, int WPE, int MODE, bool SPLIT, int NW, bool X5, int TBM = 0>
 void launch_frag(const GemmParams& p, int nsplit, hipStream_t s, int tail_bands = 0) {
   constexpr size_t lds_full = frag_lds_bytes<BM, FN, S, NW, X5>();
   constexpr size_t lds_tail = TBM > 0 ? frag_lds_bytes<(TBM > 0 ? TBM : BM), FN, S, NW, X5>() : 0;
@@ -795,7 +949,7 @@ void launch_frag(const GemmParams& p, int nsplit, hipStream_t s, int tail_bands 
   static bool attr_set = false;
   if (!attr_set) {
     DN_HIP(hipFuncSetAttribute(
-        reinterpret_cast<const void*>(&gemm_frag_kernel<BM, FN, S, D, WPE, MODE, SPLIT, PRE, NW, X5, TBM>),
+        reinterpret_cast<const void*>(&gemm_frag_kernel<BM, FN, S, D, WPE, MODE, SPLIT, NW, X5, TBM>),
         hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)));
     attr_set = true;
   }
@@ -808,31 +962,30 @@ void launch_frag(const GemmParams& p, int nsplit, hipStream_t s, int tail_bands 
              "gemm: tail tiles need no split and tile counts divisible by the XCD count");
     grid = tail_full + tail;
   }
-  hipLaunchKernelGGL((gemm_frag_kernel<BM, FN, S, D, WPE, MODE, SPLIT, PRE, NW, X5, TBM>), dim3(grid), dim3(64 * NW),
+  hipLaunchKernelGGL((gemm_frag_kernel<BM, FN, S, D, WPE, MODE, SPLIT, NW, X5, TBM>), dim3(grid), dim3(64 * NW),
                      lds, s, p, mt, nt, nsplit, tail_full, TBM > 0 ? tail_bands : 0);
   DN_HIP(hipGetLastError());
 }
 
-template <int BM, int FN, int S, int D, int WPE, int MODE, int PRE = 0, int NW = 4, bool X5 = false>
+template <int BM, int FN, int S, int D, int WPE, int MODE, int NW = 4, bool X5 = false>
 void run_frag(const GemmParams& p, int nsplit, hipStream_t s) {
   if (p.raw_partial) {
-    launch_frag<BM, FN, S, D, WPE, MODE, true, PRE, NW, X5>(p, nsplit, s);
+    launch_frag<BM, FN, S, D, WPE, MODE, true, NW, X5>(p, nsplit, s);
   } else if (nsplit > 1) {
-    launch_frag<BM, FN, S, D, WPE, MODE, true, PRE, NW, X5>(p, nsplit, s);
+    launch_frag<BM, FN, S, D, WPE, MODE, true, NW, X5>(p, nsplit, s);
     splitk_reduce(p, nsplit, s);
   } else {
-    launch_frag<BM, FN, S, D, WPE, MODE, false, PRE, NW, X5>(p, 1, s);
+    launch_frag<BM, FN, S, D, WPE, MODE, false, NW, X5>(p, 1, s);
   }
 }
 
 // Tile plans (three LDS stages): 128 x 256 (FN = 2) with two B buffers (one for the
 // convolution), two workgroups per CU; 128 x 128 (FN = 1) and 64 x 128 with two B buffers,
-// two / four workgroups per CU; 64 x 160 and 128 x 160 on five waves with three B buffers,
-// one workgroup per CU, or (stages = 5) on four waves (X5) with three / two B buffers, two
-// workgroups per CU. stages = 2 selects the 128 x 256 variant with two B buffers and one
-// workgroup per CU.
+// two / four workgroups per CU; for linear layers 64 x 160 and 128 x 160 on five waves with
+// three B buffers, one workgroup per CU; 128 x 160 on four waves (x5) with two B buffers, two
+// workgroups per CU.
 template <int MODE> void dispatch_frag(const GemmParams& p, const GemmPlan& g, hipStream_t s) {
-  if (g.bm == 128 && g.bn == 256 && g.stages == 3) {
+  if (g.bm == 128 && g.bn == 256) {
     // B two stages ahead where the registers allow it (the implicit convolution's
     // address registers do not leave room)
     if constexpr (MODE == 2) {
@@ -840,29 +993,20 @@ template <int MODE> void dispatch_frag(const GemmParams& p, const GemmPlan& g, h
     } else {
       // the last column bands of a grid with a partial last round as 64-row tiles
       if (g.tail_bands > 0 && g.split == 1 && !p.raw_partial) {
-        launch_frag<128, 2, 3, 2, 2, MODE, false, 0, 4, false, 64>(p, 1, s, g.tail_bands);
+        launch_frag<128, 2, 3, 2, 2, MODE, false, 4, false, 64>(p, 1, s, g.tail_bands);
         return;
       }
       return run_frag<128, 2, 3, 2, 2, MODE>(p, g.split, s);
     }
   }
-  if (g.bm == 128 && g.bn == 256 && g.stages == 2) return run_frag<128, 2, 3, 2, 1, MODE>(p, g.split, s);
-  if (g.bm == 128 && g.bn == 128 && g.stages == 3) return run_frag<128, 1, 3, 2, 2, MODE>(p, g.split, s);
-  if (g.bm == 64 && g.bn == 128 && g.stages == 3) return run_frag<64, 1, 3, 2, 4, MODE>(p, g.split, s);
-  if (g.bm == 64 && g.bn == 128 && g.stages == 13) return run_frag<64, 1, 3, 2, 3, MODE, 1>(p, g.split, s);
-  if (g.bm == 64 && g.bn == 128 && g.stages == 14) return run_frag<64, 1, 4, 2, 3, MODE, 1>(p, g.split, s);
-  if (g.bm == 128 && g.bn == 128 && g.stages == 13) return run_frag<128, 1, 3, 2, 2, MODE, 1>(p, g.split, s);
-  if (g.bm == 64 && g.bn == 256 && g.stages == 13) return run_frag<64, 2, 3, 2, 2, MODE, 1>(p, g.split, s);
-  if (g.bm == 32 && g.bn == 128 && g.stages == 13) return run_frag<32, 1, 3, 2, 4, MODE, 1>(p, g.split, s);
+  if (g.bm == 128 && g.bn == 128) return run_frag<128, 1, 3, 2, 2, MODE>(p, g.split, s);
+  if (g.bm == 64 && g.bn == 128) return run_frag<64, 1, 3, 2, 4, MODE>(p, g.split, s);
   if constexpr (MODE != 2) {
-    if (g.bm == 64 && g.bn == 160 && (g.stages == 3 || p.vt)) return run_frag<64, 1, 3, 3, 2, MODE, 0, 5>(p, g.split, s);
+    if (g.bm == 64 && g.bn == 160) return run_frag<64, 1, 3, 3, 2, MODE, 5>(p, g.split, s);
+    // X5 takes no V^T output
+    if (g.bm == 128 && g.bn == 160 && (!g.x5 || p.vt)) return run_frag<128, 1, 3, 3, 2, MODE, 5>(p, g.split, s);
   }
-  if (!p.vt) {
-    if (g.bm == 64 && g.bn == 160 && g.stages == 5) return run_frag<64, 1, 3, 3, 2, MODE, 0, 4, true>(p, g.split, s);
-    if (g.bm == 32 && g.bn == 160 && g.stages == 5) return run_frag<32, 1, 3, 3, 2, MODE, 0, 4, true>(p, g.split, s);
-  }
-  if (g.bm == 128 && g.bn == 160 && (g.stages == 3 || p.vt)) return run_frag<128, 1, 3, 3, 2, MODE, 0, 5>(p, g.split, s);
-  if (g.bm == 128 && g.bn == 160 && g.stages == 5) return run_frag<128, 1, 3, 2, 2, MODE, 0, 4, true>(p, g.split, s);
+  if (g.bm == 128 && g.bn == 160) return run_frag<128, 1, 3, 2, 2, MODE, 4, true>(p, g.split, s);
   throw Error(-1, "gemm: no fragment-B kernel for this tile plan");
 }
 
@@ -884,27 +1028,12 @@ __device__ __forceinline__ v8i v8i_of(const uint4& a, const uint4& b) {
   return r;
 }
 
-// Eight outputs [n, n + 8) of row m as E4M3 codes (8 bytes), or element-wise past n_store.
-__device__ __forceinline__ void store8_fp8(const GemmParams& p, int m, int n, const float v[8]) {
-  uint8_t* o = static_cast<uint8_t*>(p.out) + (long long)m * p.ldo + n;
-  if (n + 8 <= p.n_store && ((reinterpret_cast<__UINTPTR_TYPE__>(o) & 7) == 0)) {
-    uint2 w;
-    w.x = fp8x4(v[0], v[1], v[2], v[3]);
-    w.y = fp8x4(v[4], v[5], v[6], v[7]);
-    *reinterpret_cast<uint2*>(o) = w;
-  } else {
-    for (int e = 0; e < 8; ++e)
-      if (n + e < p.n_store) o[e] = static_cast<uint8_t>(fp8x4(v[e], 0.f, 0.f, 0.f) & 0xff);
-  }
-}
-
 template <int BM, int FN, int S, int WPE, bool SPLIT>
 __device__ __forceinline__ void fp8_tile(const GemmParams& p, const int m0, const int n0, const int split,
                                          const int kt0, const int kt1) {
   constexpr int NW = 4;
   constexpr int FM = BM / 32;
   constexpr int WN = 32 * FN;
-  constexpr int BN = NW * WN;
   constexpr int STAGE = BM * kRowBytes;
   constexpr int PW = BM / 32;  // DMA instructions (8 rows of 128 B) per wave per stage
   constexpr int NM = FM * FN;
@@ -1031,123 +1160,8 @@ __device__ __forceinline__ void fp8_tile(const GemmParams& p, const int m0, cons
   __builtin_amdgcn_s_waitcnt(wait_vm_lgkm0(0));
   __syncthreads();
 
-  // ---- epilogue (row-contiguous through LDS, as gemm_frag_kernel), columns scaled
-  const int col = lane & 31;
-  const int h4 = 4 * (lane >> 5);
-  const int nw0 = n0 + wave * WN;
-  constexpr int EPL = WN + 4;
-  float* ep = reinterpret_cast<float*>(smem) + wave * (32 * EPL);
-  float* slab = SPLIT ? p.part + (long long)split * p.M * p.n_store : nullptr;
-#pragma unroll
-  for (int i = 0; i < FM; ++i) {
-#pragma unroll
-    for (int j = 0; j < FN; ++j)
-#pragma unroll
-      for (int g = 0; g < 4; ++g)
-        *reinterpret_cast<f32x4*>(ep + col * EPL + j * 32 + 8 * g + h4) =
-            f32x4{acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
-    const int mb = m0 + i * 32;
-    if (SPLIT) {
-      constexpr int LPR = WN / 4;
-      constexpr int RPI = 64 / LPR;
-      const int c4 = (lane % LPR) * 4;
-      const int n = nw0 + c4;
-      float sc[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) sc[e] = n + e < p.n_store ? p.wscale[n + e] : 0.f;
-#pragma unroll
-      for (int t = 0; t < 32 / RPI; ++t) {
-        const int rr = t * RPI + lane / LPR;
-        f32x4 v4 = *reinterpret_cast<const f32x4*>(ep + rr * EPL + c4);
-        const int m = mb + rr;
-        if (m >= p.M || n >= p.n_store) continue;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v4[e] *= sc[e];
-        *reinterpret_cast<f32x4*>(slab + (long long)m * p.n_store + n) = v4;
-      }
-    } else if (!p.geglu) {
-      constexpr int LPR = WN / 8;
-      constexpr int RPI = 64 / LPR;
-      constexpr int NP = 32 / RPI;
-      const int c8 = (lane % LPR) * 8;
-      const int n = nw0 + c8;
-      const bool ncol = n < p.n_store;
-      const bool full = n + 8 <= p.n_store;
-      const bool rvec = full && p.resid && resid_vec8(p);
-      float sc[8], bias8[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        sc[e] = n + e < p.n_store ? p.wscale[n + e] : 0.f;
-        bias8[e] = p.bias && n + e < p.n_store ? p.bias[n + e] : 0.f;
-      }
-      const bool ovec = full && out_vec8(p);
-#pragma unroll
-      for (int t = 0; t < NP; ++t) {
-        const int rr = t * RPI + lane / LPR;
-        const int m = mb + rr;
-        if (m >= p.M || !ncol) continue;
-        float rs[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        if (p.resid) load_resid8(p, m, n, rvec, rs);
-        const f32x4 a0 = *reinterpret_cast<const f32x4*>(ep + rr * EPL + c8);
-        const f32x4 a1 = *reinterpret_cast<const f32x4*>(ep + rr * EPL + c8 + 4);
-        float v[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = (e < 4 ? a0[e] : a1[e - 4]) * sc[e] + bias8[e] + rs[e];
-        if (p.out_fp8)
-          store8_fp8(p, m, n, v);
-        else
-          store8(p, m, n, v, ovec);
-      }
-    } else {
-      // GEGLU over 64-column (value, gate) pair blocks, as gemm_frag_kernel
-      if constexpr (WN % 64 == 0) {
-        constexpr int LPR = WN / 16;
-        constexpr int RPI = 64 / LPR;
-        const int cq = (lane % LPR) * 8;
-        const int pb = cq / 32, c8 = cq % 32;
-        const int lc = pb * 64 + c8;
-        const int nv = nw0 + lc;
-        const int o = nw0 / 2 + cq;
-        float ba[8], bg[8], sa[8], sg[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const bool in = o < p.n_store;
-          ba[e] = in && p.bias ? p.bias[nv + e] : 0.f;
-          bg[e] = in && p.bias ? p.bias[nv + 32 + e] : 0.f;
-          sa[e] = in ? p.wscale[nv + e] : 0.f;
-          sg[e] = in ? p.wscale[nv + 32 + e] : 0.f;
-        }
-        const bool vec8 = !p.out_f32 && o + 8 <= p.n_store && out_vec8(p);
-#pragma unroll
-        for (int t = 0; t < 32 / RPI; ++t) {
-          const int rr = t * RPI + lane / LPR;
-          const f32x4 a0 = *reinterpret_cast<const f32x4*>(ep + rr * EPL + lc);
-          const f32x4 a1 = *reinterpret_cast<const f32x4*>(ep + rr * EPL + lc + 4);
-          const f32x4 g0 = *reinterpret_cast<const f32x4*>(ep + rr * EPL + lc + 32);
-          const f32x4 g1 = *reinterpret_cast<const f32x4*>(ep + rr * EPL + lc + 36);
-          const int m = mb + rr;
-          if (m >= p.M || o >= p.n_store) continue;
-          float v[8];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            v[e] = (a0[e] * sa[e] + ba[e]) * gelu_erf(g0[e] * sg[e] + bg[e]);
-            v[e + 4] = (a1[e] * sa[e + 4] + ba[e + 4]) * gelu_erf(g1[e] * sg[e + 4] + bg[e + 4]);
-          }
-          if (p.out_fp8) {
-            store8_fp8(p, m, o, v);
-          } else if (vec8) {
-            bf16x8 w;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) w[e] = static_cast<bf16>(v[e]);
-            *reinterpret_cast<bf16x8*>(static_cast<bf16*>(p.out) + (long long)m * p.ldo + o) = w;
-          } else {
-            store4<bf16>(p, m, o, v, p.n_store);
-            store4<bf16>(p, m, o + 4, v + 4, p.n_store);
-          }
-        }
-      }
-    }
-  }
+  float* ep = reinterpret_cast<float*>(smem) + wave * (32 * (WN + 4));
+  wave_epilogue<FM, FN, SPLIT, true, false>(p, acc, m0, n0 + wave * WN, split, SPLIT ? 0 : epi_kind(p), nullptr, false, ep);
 }
 
 // The fp8 kernel: unit assignment as gemm_frag_kernel (XCD-contiguous; with TBM > 0 and
@@ -1274,7 +1288,6 @@ GemmPlan gemm_plan_fp8(int M, int N, int K, int geglu, int cus, bool allow_split
   }
   while (g.split > 1 && K / 128 < 2 * g.split) --g.split;
   g.frag = 1;
-  g.stages = 3;
   // the bf16 planner's tail bands hold for the same 128 x 256 grid (two workgroups per CU)
   if (!(g.bn == 256 && g.split == 1)) g.tail_bands = 0;
   return g;

@@ -69,6 +69,41 @@ def test_linear(dtype, M, N, K):
     assert rel_l2(host(yd), ref + resh) < TOL[dtype]
 
 
+@pytest.mark.parametrize("M,N,K,off", [(70, 96, 128, 0), (129, 320, 128, 0), (129, 320, 128, 1), (1000, 1248, 192, 0),
+                                       (2048, 2048, 128, 2)])
+def test_linear_epilogue_forms(M, N, K, off):
+    """The GEMM epilogue's output kinds and their layouts (bf16): bf16 and fp32 outputs with a
+    residual of either type, ragged rows and column tails of every tile; with off elements of
+    offset on bias, residual and output none of them is 16-byte aligned (the element-wise
+    form). Bound: fp32 outputs differ from exact sums by fp32 rounding (1e-5), bf16 outputs by
+    one rounding (2^-9 relative, below TOL)."""
+    announce(f"epilogue forms M={M} N={N} K={K} off={off}")
+    r = _rng(M + N + K + off)
+    x, xh = to_dev(r.standard_normal((M, K)), dn.DN_BF16)
+    w, wh = to_dev(r.standard_normal((N, K)) / math.sqrt(K), dn.DN_BF16)
+    wp = dn.pack_weight(dn.DN_BF16, w, N, K)
+
+    def shifted(t):
+        buf = torch.zeros(t.numel() + off, device=DEV, dtype=t.dtype)
+        buf[off:].copy_(t.reshape(-1))
+        return buf[off:]
+
+    b = r.standard_normal(N).astype(np.float32)
+    bias = shifted(f32_dev(b))
+    ref = L.linear(xh, wh, b.astype(np.float64))
+    for rt in (None, torch.float32, torch.bfloat16):
+        res = None if rt is None else shifted(f32_dev(r.standard_normal((M, N))).to(rt))
+        want = ref if rt is None else ref + host(res).reshape(M, N)
+        for yt in (torch.float32, torch.bfloat16):
+            buf = torch.full((M * N + off + 8,), 7.0, device=DEV, dtype=yt)
+            y = buf[off:off + M * N]
+            dn.op_linear(dn.DN_BF16, x, wp, bias, y, M, N, K, resid=res, resid_f32=rt == torch.float32,
+                         y_f32=yt == torch.float32)
+            torch.cuda.synchronize()
+            assert rel_l2(host(y).reshape(M, N), want) < (1e-5 if yt == torch.float32 else TOL[dn.DN_BF16]), (rt, yt)
+            assert (buf[off + M * N:].float() == 7).all() and (buf[:off].float() == 7).all()
+
+
 def _interleave(w1, n):
     """GEGLU packed layout: 32-row blocks alternate value rows and gate rows."""
     out = np.empty_like(w1)
