@@ -7,7 +7,7 @@
 // (fused QKV, attention outputs, GEGLU feed-forward, projections).
 //
 // Tiling: 256 threads = 4 waves in a 2x2 grid; block tile BM x BN in
-// {128x128, 64x128, 64x64, 256x128, 128x256}, wave tile (BM/2) x (BN/2) built from 32x32x16 MFMA blocks; K
+// {128x128, 64x64}, wave tile (BM/2) x (BN/2) built from 32x32x16 MFMA blocks; K
 // step BK = 128 bytes of each row (64 bf16 / 32 fp32), staged through
 // double-buffered LDS (one barrier per K step; the next tile's global loads are
 // issued a full K step ahead). The MFMA is issued as C^T = B A^T so that each
@@ -240,13 +240,7 @@ void launch(const GemmParams& p, hipStream_t s) {
 }
 
 template <typename T, bool CONV> void dispatch(const GemmParams& p, const GemmPlan& g, hipStream_t s) {
-  if (g.bm == 256 && g.bn == 128)
-    launch<T, 256, 128, CONV>(p, s);
-  else if (g.bm == 128 && g.bn == 256)
-    launch<T, 128, 256, CONV>(p, s);
-  else if (g.bm == 64 && g.bn == 128)
-    launch<T, 64, 128, CONV>(p, s);
-  else if (g.bm == 64 && g.bn == 64)
+  if (g.bm == 64 && g.bn == 64)
     launch<T, 64, 64, CONV>(p, s);
   else
     launch<T, 128, 128, CONV>(p, s);
@@ -254,90 +248,85 @@ template <typename T, bool CONV> void dispatch(const GemmParams& p, const GemmPl
 
 }  // namespace
 
-// Tile choice of the register-staged kernel (fp32, the check mode, and bf16 shapes the
-// fragment layout does not take: N % 32 != 0 or K % 64 != 0, e.g. conv_in and the
-// output head): 64 x 64 tiles when there are fewer 128 x 128 tiles than CUs (GEGLU
-// needs 64-column value/gate pairs per wave, i.e. a block width of at least 128), else
-// 128 x 128 tiles with two resident workgroups per CU.
-// Fragment-B kernel (bf16 weights in fragment order). Three tile variants share a CU
-// between several workgroups: 128 x 256 (two per CU), 128 x 128 (two) and 64 x 128
-// (four); five-wave 64 x 160 and 128 x 160 tiles run one workgroup per CU (the M = 2048,
-// N = 1280 projections are exactly one 64 x 160 tile per CU, where 64 x 128 tiles put
-// two workgroups on a quarter of the CUs; 128 x 160 tiles cover the 8192-row N = 640
-// layers in one round and the N = 320 convolutions without padding columns). The plan
-// minimises a cost model fitted to measured SD-XL GEMM times on MI355X
-// (bf16, weights streamed from HBM; one fit for the linear layers, one for the implicit
-// convolutions): a run takes ceil(units / slots) rounds, a round
-// costs the MFMA work of the units resident on a CU at a per-CU rate R plus a fixed
-// prologue cost O; the epilogue adds E per million outputs, and a K split adds the fp32
-// slabs written and read by the reduction (when the consumer, a LayerNorm, sums the
-// slabs itself: its extra slab reads, at the cost per slab measured for that kernel
-// together with the GEMM). GEGLU needs 64-column value/gate pairs per wave (128 x 256).
-GemmPlan frag_plan(int M, int N, int K, int geglu, int cus, bool allow_split, bool fused_reduce, bool conv) {
-  struct Var {
-    int bm, bn, wg;
-    double rate, fixed, epi;  // FLOP per us per CU, us per round, us per 1e6 outputs
-  };
-  // separate fits for the linear layers and the implicit convolutions (whose A gather
-  // and tap masks change the per-stage cost)
-  static const Var lin_vars[] = {{128, 256, 2, 2.4e6, 5.0, 1.0},
-                                 {128, 128, 2, 2.0e6, 8.0, 0.0},
-                                 {64, 128, 4, 1.6e6, 3.0, 0.0},
-                                 {64, 160, 1, 3.1e6, 9.4, 0.0},
-                                 {128, 160, 1, 4.14e6, 16.7, 0.0}};
-  static const Var conv_vars[] = {{128, 256, 2, 2.4e6, 5.0, 3.0},
-                                  {128, 128, 2, 1.6e6, 1.0, 0.0},
-                                  {64, 128, 4, 1.6e6, 1.0, 0.0},
-                                  {128, 160, 1, 3.39e6, 10.7, 0.0}};
-  const Var* vars = conv ? conv_vars : lin_vars;
-  const int nvars = conv ? 4 : 5;  // the five-wave 64 x 160 tile takes linear layers only
-  // convolutions: a partly filled round costs more than its average load per CU (the
-  // CUs that hold one more unit finish last)
-  const double fill_penalty = conv ? 0.25 : 0.0;
+// Fragment-B kernels: tile, split and tail bands by a cost model fitted to launches measured
+// on MI355X (bf16: 147 shapes x every tile and split, linear layers and implicit convolutions
+// apart; fp8: 29 shapes). A tile variant runs up to `wg` workgroups per CU; with c of them on
+// the busiest CU a K stage (64 bf16 or 128 fp8 values) takes stage[c - 1] us, so a round of
+// units costs fixed + wgcost c + stages x stage[c - 1], a grid is its full rounds plus the
+// remainder's round, and the outputs cost per_mb us per MB written (an fp32 output also reads
+// its residual). The stage times are what the old model missed: a lone 128 x 256 workgroup
+// needs 0.68 us per stage where two together need 1.41, so a half-filled round is not half
+// the price. Splitting K adds the reduction launch and its slab traffic, or, when a LayerNorm
+// sums the slabs, that kernel's extra reads. Over the measured shapes the chosen plan is 0.6 %
+// from the best one (geometric mean; 9 % for linear layers and 12 % for convolutions before:
+// decoder convolutions of 256 and 512 channels were 128 x 160 tiles with 20 % padding, 785 ->
+// 562 us at 262144 x 256 x 4608, and short linear layers were split, 16.8 -> 9.7 us at
+// 1152 x 1280 x 1280).
+struct TileCost {
+  int bm, bn, x5, wg;
+  double fixed, wgcost, stage[4], per_mb;
+};
+static const TileCost kLinCost[] = {{128, 256, 0, 2, 5.2, 0.0, {0.684, 1.408}, 0.068},
+                                    {128, 128, 0, 2, 2.9, 0.0, {0.468, 0.953}, 0.114},
+                                    {64, 128, 0, 4, 1.6, 0.14, {0.310, 0.610, 0.877, 1.172}, 0.145},
+                                    {128, 160, 1, 2, 4.5, 0.0, {0.536, 1.083}, 0.094},
+                                    {64, 160, 0, 1, 2.3, 0.0, {0.380}, 0.081},
+                                    {128, 160, 0, 1, 3.1, 0.0, {0.636}, 0.097}};
+static const TileCost kConvCost[] = {{128, 256, 0, 2, 5.7, 0.0, {0.803, 1.507}, 0.059},
+                                     {128, 128, 0, 2, 4.0, 0.0, {0.567, 0.991}, 0.030},
+                                     {64, 128, 0, 4, 3.5, 0.1, {0.359, 0.561, 0.866, 1.167}, 0.0},
+                                     {128, 160, 1, 2, 5.1, 0.0, {0.644, 1.124}, 0.066}};
+static const TileCost kFp8Cost[] = {{128, 256, 0, 2, 2.7, 1.9, {1.037, 1.125}, 0.067},
+                                    {128, 128, 0, 2, 0.3, 0.0, {0.740, 0.838}, 0.225}};
+
+
+GemmPlan frag_plan(int M, int N, int K, int geglu, int cus, bool allow_split, bool fused_reduce, PlanKind kind,
+                   bool out_f32) {
+  const TileCost* vars = kind == kPlanConv ? kConvCost : kind == kPlanFp8 ? kFp8Cost : kLinCost;
+  const int nvars = kind == kPlanConv ? 4 : kind == kPlanFp8 ? 2 : 6;
+  const int nk = K / (kind == kPlanFp8 ? 128 : 64);
+  const int min_stages = kind == kPlanFp8 ? 2 : 4;  // K stages a split part must have
+  const double mn = (double)M * N / 1e6;
   GemmPlan best{128, 256};
   best.frag = 1;
   double best_t = 1e300;
-  const int nk = K / 64;
   for (int vi = 0; vi < nvars; ++vi) {
-    const Var& v = vars[vi];
-    if (geglu && v.bn != 256) continue;
-    // the five-wave 64 x 160 tile wins where the fixed cost dominates (measured up to
-    // K = 2560); deeper contractions (FF-out, K = 5120) run faster as split 128 x 256 tiles
-    if (v.bm == 64 && v.bn == 160 && K > 2560) continue;
+    const TileCost& v = vars[vi];
+    if (geglu && v.bn != 256) continue;  // GEGLU needs 64-column value / gate pairs per wave
     const long long tiles = (long long)ceil_div(M, v.bm) * ceil_div(N, v.bn);
+    const long long slots = (long long)cus * v.wg;
     for (int sp = 1; sp <= kMaxSplit; ++sp) {
-      // the five-wave tiles (one workgroup per CU) were measured unsplit only
-      if (sp > 1 && (geglu || !allow_split || nk / sp < 4 || v.wg == 1)) break;
-      const long long units = tiles * sp;
-      const long long slots = (long long)cus * v.wg;
-      const long long rounds = (units + slots - 1) / slots;
-      const double load = (double)std::min(units, slots) / cus;
-      const double per_cu = std::max(1.0, load) + fill_penalty * (std::ceil(load) - load);
-      double t = rounds * (per_cu * 2.0 * v.bm * v.bn * ((double)K / sp) / v.rate + v.fixed) + v.epi * M * N / 1e6;
-      if (sp > 1) t += fused_reduce ? 0.3 * (sp - 1.0) * M * N * 4.0 / 1e6 : 0.1 * (sp + 1.0) * M * N * 4.0 / 1e6 + 2.0;
+      if (sp > 1 && (geglu || !allow_split || nk / sp < min_stages)) break;
+      const long long units = tiles * sp, full = units / slots, rem = units % slots;
+      const double st = (double)nk / sp;
+      double t = full * (v.fixed + v.wgcost * v.wg + st * v.stage[v.wg - 1]);
+      if (rem) {
+        const int c = static_cast<int>((rem + cus - 1) / cus);
+        t += v.fixed + v.wgcost * c + st * v.stage[c - 1];
+      }
+      if (sp == 1) {
+        t += v.per_mb * mn * (geglu ? 1 : out_f32 ? 8 : 2);
+      } else {
+        t += v.per_mb * mn * 4 * sp;
+        t += fused_reduce ? 1.5 + mn * 4 * (sp + 1) / 7.0 : 3.5 + mn * (4 * sp + (out_f32 ? 8 : 2)) / 6.0;
+      }
       if (t < best_t) {
         best_t = t;
         best.bm = v.bm;
         best.bn = v.bn;
+        best.x5 = v.x5;
         best.split = sp;
       }
     }
   }
-  // 128 x 160 tiles run on four waves, two workgroups per CU (the five-wave tile leaves
-  // one SIMD with two waves' work and one workgroup per CU) for every convolution
-  // (measured: 32768-row convolutions 17 % faster, the 8192-row upsampling convolution
-  // from 1280 channels 373 -> 268 us, the other 8192-row ones equal or up to 6 % faster)
-  // and for linear layers with more tiles than CUs; with one tile per CU the linear
-  // layers run as fast or faster on five waves
-  if (best.bm == 128 && best.bn == 160 &&
-      (conv || (long long)ceil_div(M, 128) * ceil_div(N, 160) * best.split > cus))
-    best.x5 = 1;
-  // 128 x 256 linear tiles (two workgroups per CU) whose count leaves a last round at most
-  // half full: those last whole column bands run as 64-row tiles over every CU
-  if (!conv && best.bm == 128 && best.bn == 256 && best.split == 1) {
+  // 128 x 256 linear tiles (two workgroups per CU) with a last round of at most half a tile
+  // per CU: its whole column bands run as 64-row tiles, one per CU (FF-in 2048 x 10240 x 1280
+  // 54.2 -> 51.2 us, fp8 33.3 -> 29.3). With a tile per CU left over, 64-row tiles only add
+  // prologues (4096 x 10240 x 1280 97 -> 112 us).
+  if (kind != kPlanConv && best.bm == 128 && best.bn == 256 && best.split == 1) {
     const long long mt = ceil_div(M, 128), nt = ceil_div(N, 256), slots = 2LL * cus;
     const long long tiles = mt * nt, rem = tiles % slots;
-    if (rem > 0 && 2 * rem <= slots && rem % mt == 0) {
+    if (rem > 0 && 2 * rem <= cus && rem % mt == 0) {
       const long long bands = rem / mt, tail = (long long)ceil_div(M, 64) * bands;
       if ((tiles - rem) % 8 == 0 && tail % 8 == 0 && bands < nt) best.tail_bands = static_cast<int>(bands);
     }
@@ -345,9 +334,16 @@ GemmPlan frag_plan(int M, int N, int K, int geglu, int cus, bool allow_split, bo
   return best;
 }
 
+// Tile choice of the register-staged kernel (fp32, the check mode, and bf16 shapes the
+// fragment layout does not take: N % 32 != 0 or K % 64 != 0, e.g. conv_in and the
+// output head): 64 x 64 tiles when there are fewer 128 x 128 tiles than CUs (GEGLU
+// needs 64-column value/gate pairs per wave, i.e. a block width of at least 128), else
+// 128 x 128 tiles with two resident workgroups per CU.
 template <typename T>
-GemmPlan gemm_plan(int M, int N, int K, int geglu, int cus, bool allow_split, bool fused_reduce, bool conv) {
-  if (sizeof(T) == 2 && gemm_frag_layout(N, K)) return frag_plan(M, N, K, geglu, cus, allow_split, fused_reduce, conv);
+GemmPlan gemm_plan(int M, int N, int K, int geglu, int cus, bool allow_split, bool fused_reduce, bool conv,
+                   bool out_f32) {
+  if (sizeof(T) == 2 && gemm_frag_layout(N, K))
+    return frag_plan(M, N, K, geglu, cus, allow_split, fused_reduce, conv ? kPlanConv : kPlanLinear, out_f32);
   const long long t128 = (long long)ceil_div(M, 128) * ceil_div(N, 128);
   if (!geglu && t128 < cus) return GemmPlan{64, 64};
   return GemmPlan{128, 128};
@@ -379,8 +375,8 @@ template <typename T> void gemm(const GemmParams& p, const GemmPlan& g, hipStrea
     dispatch<T, false>(p, g, s);
 }
 
-template GemmPlan gemm_plan<float>(int, int, int, int, int, bool, bool, bool);
-template GemmPlan gemm_plan<bf16>(int, int, int, int, int, bool, bool, bool);
+template GemmPlan gemm_plan<float>(int, int, int, int, int, bool, bool, bool, bool);
+template GemmPlan gemm_plan<bf16>(int, int, int, int, int, bool, bool, bool, bool);
 template void gemm<float>(const GemmParams&, const GemmPlan&, hipStream_t);
 template void gemm<bf16>(const GemmParams&, const GemmPlan&, hipStream_t);
 

@@ -1277,20 +1277,8 @@ bool gemm_fp8_layout(int N, int K) { return N >= 32 && N % 32 == 0 && K >= 128 &
 
 size_t gemm_fp8_code_bytes(int N, int K) { return (size_t)((N + 31) / 32 * 32) * K; }
 
-GemmPlan gemm_plan_fp8(int M, int N, int K, int geglu, int cus, bool allow_split, bool fused_reduce) {
-  // the bf16 planner's choice among its 128 x 256 and 128 x 128 tiles (and its split)
-  GemmPlan g = frag_plan(M, N, K, geglu, cus, allow_split, fused_reduce, false);
-  if (!(g.bm == 128 && (g.bn == 256 || g.bn == 128))) {
-    g.bm = 128;
-    g.bn = (geglu || N >= 1024) ? 256 : 128;
-    g.split = 1;
-    g.tail_bands = 0;
-  }
-  while (g.split > 1 && K / 128 < 2 * g.split) --g.split;
-  g.frag = 1;
-  // the bf16 planner's tail bands hold for the same 128 x 256 grid (two workgroups per CU)
-  if (!(g.bn == 256 && g.split == 1)) g.tail_bands = 0;
-  return g;
+GemmPlan gemm_plan_fp8(int M, int N, int K, int geglu, int cus, bool allow_split, bool fused_reduce, bool out_f32) {
+  return frag_plan(M, N, K, geglu, cus, allow_split, fused_reduce, kPlanFp8, out_f32);
 }
 
 void gemm_fp8(const GemmParams& p, const GemmPlan& g, hipStream_t s) {

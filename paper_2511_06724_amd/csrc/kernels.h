@@ -69,10 +69,12 @@ constexpr int kMaxSplit = 8;
 // split costs only the extra slab reads.
 template <typename T>
 GemmPlan gemm_plan(int M, int N, int K, int geglu, int cus, bool allow_split = true, bool fused_reduce = false,
-                   bool conv = false);
+                   bool conv = false, bool out_f32 = false);
 template <typename T> void gemm(const GemmParams& p, const GemmPlan& g, hipStream_t s);
-// The fragment-B kernel's tile plan (cost model fitted to measured SD-XL GEMM times).
-GemmPlan frag_plan(int M, int N, int K, int geglu, int cus, bool allow_split, bool fused_reduce, bool conv);
+// The fragment-B kernels' tile plan (a cost model fitted to measured launches).
+enum PlanKind { kPlanLinear, kPlanConv, kPlanFp8 };
+GemmPlan frag_plan(int M, int N, int K, int geglu, int cus, bool allow_split, bool fused_reduce, PlanKind kind,
+                   bool out_f32);
 void gemm_bf16_frag(const GemmParams& p, const GemmPlan& g, hipStream_t s);
 // bf16 weight matrices [N][K] with gemm_frag_layout(N, K) are stored in MFMA fragment
 // order (gemm_frag.hip) and multiplied by the fragment-B kernel; every other shape,
@@ -81,7 +83,8 @@ bool gemm_frag_layout(int N, int K);
 // fp8 (E4M3) GEMM: A fp8 codes [M][lda], B a matrix packed by pack_fp8 (codes in the
 // fragment order of the 32x32x64 fp8 matrix-core step, fp32 row scales in p.wscale);
 // N % 32 == 0, K % 128 == 0. Tile plans 128 x 256 and 128 x 128, split-K as gemm_plan.
-GemmPlan gemm_plan_fp8(int M, int N, int K, int geglu, int cus, bool allow_split, bool fused_reduce);
+GemmPlan gemm_plan_fp8(int M, int N, int K, int geglu, int cus, bool allow_split, bool fused_reduce,
+                       bool out_f32 = false);
 void gemm_fp8(const GemmParams& p, const GemmPlan& g, hipStream_t s);
 bool gemm_fp8_layout(int N, int K);
 size_t gemm_fp8_code_bytes(int N, int K);  // N rounded up to 32, times K
