@@ -239,7 +239,154 @@ void launch(const GemmParams& p, hipStream_t s) {
   DN_HIP(hipGetLastError());
 }
 
+// fp32 GEMM for grids too small to fill the chip: a workgroup owns one 32 x 32 tile (with
+// GEGLU, 32 value and the matching 32 gate columns) and its eight waves split K. Bound by
+// latency, not by rate: 512 x 64 x 576 (a 3x3 convolution of the 16 x 16 denoiser) is 8 tiles
+// of 64 x 64, whose four waves walk K alone (21.4 us per launch); 32 tiles of eight waves each
+// run an eighth of K (10.2 us; GEGLU 512 x 2 x 256 x 64 13.0 -> 9.1 us).
+// Operands come straight from global memory: lane l takes four consecutive k (16 bytes) at
+// 4 (l / 32) of an 8-deep step for row l % 32 of A and of B, and MFMA e of the step contracts
+// component e of both (any k order common to both operands gives the same sum). Two sets of
+// kWsSteps steps, the next loaded while the current one is multiplied. The partial tiles meet
+// in LDS in wave order (deterministic).
+constexpr int kWsWaves = 8, kWsSteps = 3;
+
+template <bool CONV, int NB>
+__global__ __launch_bounds__(64 * kWsWaves) void gemm_wavesplit_kernel(GemmParams p, int mt) {
+  using MM = Mma<float>;
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  float* red = reinterpret_cast<float*>(smem_raw);  // [wave][NB][16][64]
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int n_tile = blockIdx.x / mt, m_tile = blockIdx.x - n_tile * mt;
+  const int m0 = m_tile * 32, n0 = n_tile * 32 * NB;
+  const int k4 = 4 * (lane >> 5);
+  const int m = min(m0 + (lane & 31), p.M - 1);
+  const float* bp[NB];
+#pragma unroll
+  for (int j = 0; j < NB; ++j)
+    bp[j] = static_cast<const float*>(p.b) + (long long)min(n0 + 32 * j + (lane & 31), p.N - 1) * p.ldb + k4;
+  const int ct = p.c0 + p.c1;
+  int smp = 0, iy0 = 0, ix0 = 0;
+  const int hl = p.in_h << p.up, wl = p.in_w << p.up;
+  if (CONV) {
+    const int opix = p.out_h * p.out_w;
+    smp = m / opix;
+    const int r2 = m - smp * opix, oy = r2 / p.out_w;
+    iy0 = oy * p.stride - 1;
+    ix0 = (r2 - oy * p.out_w) * p.stride - 1;
+  }
+  const int ns = p.K / 8;
+  const int s0 = ns * wave / kWsWaves, s1 = ns * (wave + 1) / kWsWaves;
+  // the wave's steps past s1 read its last step again and are not multiplied
+  auto load = [&](int st, f32x4& a, f32x4 (&b)[NB]) {
+    const int k = 8 * min(st, s1 - 1);
+    int tap = 0, c = k;
+    if (CONV) {
+      tap = k / ct;
+      c = k - tap * ct;
+    }
+    const bool first = c < p.c0;
+    const float* src = static_cast<const float*>(first ? p.a0 : p.a1);
+    const int ld = first ? p.lda0 : p.lda1, cc = (first ? c : c - p.c0) + k4;
+    if (CONV) {
+      const int ky = tap / 3, iy = iy0 + ky, ix = ix0 + tap - 3 * ky;
+      const bool in = iy >= 0 && iy < hl && ix >= 0 && ix < wl;
+      const long long pix = in ? (long long)(smp * p.in_h + (iy >> p.up)) * p.in_w + (ix >> p.up) : 0;
+      const f32x4 v = *reinterpret_cast<const f32x4*>(src + pix * ld + cc);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) a[e] = in ? v[e] : 0.f;
+    } else {
+      a = *reinterpret_cast<const f32x4*>(src + (long long)m * ld + cc);
+    }
+#pragma unroll
+    for (int j = 0; j < NB; ++j) b[j] = *reinterpret_cast<const f32x4*>(bp[j] + k);
+  };
+  f32x16 acc[NB];
+#pragma unroll
+  for (int j = 0; j < NB; ++j)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
+  if (s0 < s1) {
+    f32x4 a[2][kWsSteps], b[2][kWsSteps][NB];
+    auto load_set = [&](int st, int u) {
+#pragma unroll
+      for (int t = 0; t < kWsSteps; ++t) load(st + t, a[u][t], b[u][t]);
+    };
+    auto mma_set = [&](int st, int u) {
+#pragma unroll
+      for (int t = 0; t < kWsSteps; ++t)
+        if (st + t < s1) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int j = 0; j < NB; ++j) acc[j] = MM::mma(b[u][t][j][e], a[u][t][e], acc[j]);
+        }
+    };
+    load_set(s0, 0);
+    for (int st = s0; st < s1; st += 2 * kWsSteps) {
+      load_set(st + kWsSteps, 1);
+      mma_set(st, 0);
+      load_set(st + 2 * kWsSteps, 0);
+      mma_set(st + kWsSteps, 1);
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < NB; ++j)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) red[((wave * NB + j) * 16 + r) * 64 + lane] = acc[j][r];
+  __syncthreads();
+  // thread: four columns 8 g + 4 (l / 32) .. of row l % 32
+  if (threadIdx.x >= 256) return;
+  const int g = threadIdx.x >> 6, h4 = 4 * (lane >> 5);
+  float v[NB][4];
+#pragma unroll
+  for (int j = 0; j < NB; ++j)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      float x = red[(j * 16 + 4 * g + e) * 64 + lane];
+#pragma unroll
+      for (int w = 1; w < kWsWaves; ++w) x += red[((w * NB + j) * 16 + 4 * g + e) * 64 + lane];
+      v[j][e] = x;
+    }
+  const int row = m0 + (lane & 31);
+  if (row >= p.M) return;
+  if constexpr (NB == 2) {
+    const int nv = n0 + 8 * g + h4, o = n0 / 2 + 8 * g + h4;  // value column (gate 32 further), output column
+    if (o >= p.n_store) return;
+    float y[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      y[e] = (v[0][e] + (p.bias ? p.bias[nv + e] : 0.f)) * gelu_erf(v[NB - 1][e] + (p.bias ? p.bias[nv + 32 + e] : 0.f));
+    store4<float>(p, row, o, y, p.n_store);
+  } else {
+    epilogue_group<float>(p, row, n0 + 8 * g + h4, v[0]);
+  }
+}
+
+template <bool CONV, int NB> void launch_wavesplit(const GemmParams& p, hipStream_t s) {
+  const int mt = ceil_div(p.M, 32), nt = ceil_div(p.N, 32 * NB);
+  const size_t lds = sizeof(float) * kWsWaves * NB * 16 * 64;
+  static bool attr_set = false;
+  if (!attr_set) {
+    DN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_wavesplit_kernel<CONV, NB>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)));
+    attr_set = true;
+  }
+  hipLaunchKernelGGL((gemm_wavesplit_kernel<CONV, NB>), dim3(mt * nt), dim3(64 * kWsWaves), lds, s, p, mt);
+  DN_HIP(hipGetLastError());
+}
+
 template <typename T, bool CONV> void dispatch(const GemmParams& p, const GemmPlan& g, hipStream_t s) {
+  if constexpr (sizeof(T) == 4) {
+    if (g.bm == 32) {
+      if (p.geglu)
+        launch_wavesplit<CONV, 2>(p, s);
+      else
+        launch_wavesplit<CONV, 1>(p, s);
+      return;
+    }
+  }
   if (g.bm == 64 && g.bn == 64)
     launch<T, 64, 64, CONV>(p, s);
   else
@@ -344,6 +491,8 @@ GemmPlan gemm_plan(int M, int N, int K, int geglu, int cus, bool allow_split, bo
                    bool out_f32) {
   if (sizeof(T) == 2 && gemm_frag_layout(N, K))
     return frag_plan(M, N, K, geglu, cus, allow_split, fused_reduce, conv ? kPlanConv : kPlanLinear, out_f32);
+  // fp32 with fewer 64 x 64 tiles than CUs: 32-column tiles whose waves split K
+  if (sizeof(T) == 4 && (long long)ceil_div(M, 64) * ceil_div(N, 64) < cus) return GemmPlan{32, geglu ? 64 : 32};
   const long long t128 = (long long)ceil_div(M, 128) * ceil_div(N, 128);
   if (!geglu && t128 < cus) return GemmPlan{64, 64};
   return GemmPlan{128, 128};
@@ -359,7 +508,7 @@ template <typename T> void gemm(const GemmParams& p, const GemmPlan& g, hipStrea
   DN_CHECK(p.taps == 1 || (p.c0 + p.c1) % BK == 0, "gemm: conv channels must be a multiple of the K tile");
   DN_CHECK(p.a0 && p.b && p.out && (p.c1 == 0 || p.a1), "gemm: null operand");
   DN_CHECK(!p.geglu || (p.N % 64 == 0), "gemm: GEGLU needs N % 64 == 0");
-  DN_CHECK(!p.geglu || (g.bn / 2) % 64 == 0,
+  DN_CHECK(!p.geglu || g.bm == 32 || (g.bn / 2) % 64 == 0,
            "gemm: GEGLU needs 64-column value/gate pairs per wave");
   DN_CHECK(p.ldb % (16 / (int)sizeof(T)) == 0 && p.lda0 % (16 / (int)sizeof(T)) == 0 &&
                (p.c1 == 0 || p.lda1 % (16 / (int)sizeof(T)) == 0),

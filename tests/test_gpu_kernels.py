@@ -104,6 +104,22 @@ def test_linear_epilogue_forms(M, N, K, off):
             assert (buf[off + M * N:].float() == 7).all() and (buf[:off].float() == 7).all()
 
 
+@pytest.mark.parametrize("M,N,K", [(1, 4, 32), (33, 30, 32), (31, 100, 96), (70, 33, 64), (512, 64, 576), (1000, 65, 160)])
+def test_linear_fp32_small(M, N, K):
+    """fp32 grids below the CU count (32-column tiles whose eight waves split K): fewer K
+    steps than waves, uneven shares, ragged rows and columns, with a residual. Exact products,
+    fp32 sums: TOL."""
+    announce(f"linear fp32 small M={M} N={N} K={K}")
+    r = _rng(M + N + K)
+    x, w = r.standard_normal((M, K)).astype(np.float32), r.standard_normal((N, K)).astype(np.float32)
+    b, res = r.standard_normal(N).astype(np.float32), r.standard_normal((M, N)).astype(np.float32)
+    y = torch.empty((M, N), device=DEV)
+    dn.op_linear(dn.DN_FP32, f32_dev(x), f32_dev(w), f32_dev(b), y, M, N, K, resid=f32_dev(res), resid_f32=True, y_f32=True)
+    torch.cuda.synchronize()
+    ref = L.linear(x.astype(np.float64), w.astype(np.float64), b.astype(np.float64)) + res
+    assert rel_l2(host(y), ref) < TOL[dn.DN_FP32]
+
+
 def _interleave(w1, n):
     """GEGLU packed layout: 32-row blocks alternate value rows and gate rows."""
     out = np.empty_like(w1)
@@ -247,7 +263,9 @@ def test_linear_vt(dtype, M, seq, heads, dp, K):
 
 
 @pytest.mark.parametrize("dtype", DT)
-@pytest.mark.parametrize("n,HW,C,G,silu", [(2, 300, 320, 32, 1), (2, 64, 64, 32, 0), (1, 1000, 1920, 32, 1),
+@pytest.mark.parametrize("n,HW,C,G,silu", [(1, 1, 64, 32, 0), (2, 204, 1280, 32, 1), (2, 1224, 640, 32, 1), (2, 1225, 640, 32, 1),
+                                            (3, 1023, 2560, 32, 1), (2, 100, 64, 64, 1), (1, 50, 24, 3, 0),
+                                            (2, 300, 320, 32, 1), (2, 64, 64, 32, 0), (1, 1000, 1920, 32, 1),
                                             (2, 1024, 1280, 32, 1), (2, 4096, 640, 32, 0), (1, 16384, 320, 32, 1),
                                             (2, 200, 96, 32, 1), (2, 1024, 2560, 32, 1)])
 def test_groupnorm(dtype, n, HW, C, G, silu):
@@ -255,7 +273,9 @@ def test_groupnorm(dtype, n, HW, C, G, silu):
     128x128, and the 2560-channel concatenation at 32x32), an odd channel count per group
     (96 / 32 = 3), and both apply mappings: one channel vector per thread (at most 256
     16-byte vectors per pixel) and (pixel, vector) pairs (fp32 from 1280 channels, bf16 at
-    2560)."""
+    2560); the one-launch form at one pixel, at the last size it takes and the first it does
+    not (1224 and 1225 pixels of 640 channels in bf16), with one channel per group and with
+    groups that share a 16-byte vector."""
     announce(f"groupnorm dtype={dtype} n={n} HW={HW} C={C} silu={silu}")
     r = _rng(n + HW + C)
     x, xh = to_dev(0.5 + 2.0 * r.standard_normal((n, HW, C)), dtype)
