@@ -1,6 +1,6 @@
 // GroupNorm (+SiLU) and LayerNorm kernels (HBM-bound; gfx950).
 //
-// GroupNorm on NHWC activations runs in three launches:
+// GroupNorm on NHWC activations: small images in one launch (gn_one_kernel), else three:
 //   1. partial: each workgroup reduces a chunk of pixels of one sample and a slice of
 //      up to 256 channel vectors into fp32 sums of x and x^2 per group (16-byte
 //      coalesced loads; a thread owns one 16-byte channel vector, so its accumulators
@@ -305,6 +305,150 @@ __global__ __launch_bounds__(256) void gn_apply_cv_kernel(GroupNormParams p, GnG
   }
 }
 
+// GroupNorm in one launch for images small enough that a workgroup holds every pixel of a
+// channel slice in registers: one 1024-thread workgroup per (slice, sample), a slice being the
+// fewest whole groups that make whole 16-byte vectors (and at least 32 bytes). A thread owns
+// one of the slice's sv vectors and up to VPT pixels, all loaded before the first is used.
+// Bound by latency: the three launches (statistics, merge, apply) each wait on memory and on
+// the launch before; here the tensor is read once and the statistics meet in LDS. Measured,
+// three launches -> one: 2 x 1024 x 1280 bf16 13.0 -> 9.6 us, 2 x 1024 x 640 12.8 -> 8.3,
+// 2 x 576 x 1280 12.4 -> 7.3, 2 x 256 x 64 fp32 12.9 -> 7.7.
+// Sums of x and x^2 in fp32 per thread (VPT pixels of the group's channels in its vector) and,
+// by a DPP tree, over the wave; the sixteen waves in fp64: fewer fp32 terms in a row than the
+// chunk sums of gn_partial_kernel. A fixed order, so the result is deterministic.
+constexpr int kGnOneThreads = 1024;
+constexpr int kGnOneWaves = kGnOneThreads / 64;
+constexpr int kGnOneMaxVec = 12;     // vectors per thread
+constexpr int kGnOneMaxGroups = 16;  // groups per slice
+
+template <typename T, int VPT>
+__global__ __launch_bounds__(kGnOneThreads) void gn_one_kernel(GroupNormParams p, int C, int sgroups, int sv) {
+  constexpr int VEC = Elem<T>::kVec;
+  __shared__ float part[kGnOneMaxGroups][2][kGnOneWaves];
+  __shared__ double stat[kGnOneMaxGroups][2];  // mean, 1 / deviation
+  const int cg = C / p.G;
+  const int pls = kGnOneThreads / sv;  // pixel lanes
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int n = blockIdx.y;
+  const int pl = tid / sv, col = tid - (tid / sv) * sv;
+  const bool active = pl < pls;
+  const int cs = (active ? col : 0) * VEC;  // first channel in the slice
+  const int c = blockIdx.x * sgroups * cg + cs;
+  const bool first = c < p.c0;
+  const T* src = first ? static_cast<const T*>(p.x0) + c : static_cast<const T*>(p.x1) + (c - p.c0);
+  const int ld = first ? p.c0 : p.c1;
+  uint4 raw[VPT];
+#pragma unroll
+  for (int t = 0; t < VPT; ++t) {
+    const int px = min(pl + t * pls, p.HW - 1);
+    raw[t] = ld16(src + ((long long)n * p.HW + px) * ld);
+  }
+  float gam[VEC], bet[VEC];
+#pragma unroll
+  for (int e = 0; e < VEC; ++e) {
+    gam[e] = p.gamma[c + e];
+    bet[e] = p.beta[c + e];
+  }
+  float s[VEC], q[VEC];
+#pragma unroll
+  for (int e = 0; e < VEC; ++e) s[e] = q[e] = 0.f;
+#pragma unroll
+  for (int t = 0; t < VPT; ++t) {
+    const bool in = active && pl + t * pls < p.HW;
+    const T* xv = reinterpret_cast<const T*>(&raw[t]);
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) {
+      const float x = in ? to_f32(xv[e]) : 0.f;
+      s[e] += x;
+      q[e] += x * x;
+    }
+  }
+  for (int g = 0; g < sgroups; ++g) {
+    float a = 0.f, b = 0.f;
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) {
+      const bool mine = (unsigned)(cs + e - g * cg) < (unsigned)cg;
+      a += mine ? s[e] : 0.f;
+      b += mine ? q[e] : 0.f;
+    }
+    a = wave_sum_dpp(a);
+    b = wave_sum_dpp(b);
+    if (lane == 0) {
+      part[g][0][wave] = a;
+      part[g][1][wave] = b;
+    }
+  }
+  __syncthreads();
+  if (tid < sgroups) {
+    double a = 0.0, b = 0.0;
+#pragma unroll
+    for (int w = 0; w < kGnOneWaves; ++w) {
+      a += part[tid][0][w];
+      b += part[tid][1][w];
+    }
+    const double cnt = (double)cg * p.HW, mean = a / cnt;
+    stat[tid][0] = mean;
+    stat[tid][1] = 1.0 / sqrt(fmax(b / cnt - mean * mean, 0.0) + (double)p.eps);
+  }
+  __syncthreads();
+  if (!active) return;
+  float scale[VEC], shift[VEC];
+#pragma unroll
+  for (int e = 0; e < VEC; ++e) {
+    const int g = (cs + e) / cg;
+    const double a = (double)gam[e] * stat[g][1];
+    scale[e] = (float)a;
+    shift[e] = (float)((double)bet[e] - stat[g][0] * a);
+  }
+  T* dst = static_cast<T*>(p.y) + (long long)n * p.HW * C + c;
+#pragma unroll
+  for (int t = 0; t < VPT; ++t) {
+    const int px = pl + t * pls;
+    if (px >= p.HW) continue;
+    // opaque: the pixels stay packed between the two uses (converted values kept in fp32
+    // would take twice the registers and spill)
+    asm volatile("" : "+v"(raw[t].x), "+v"(raw[t].y), "+v"(raw[t].z), "+v"(raw[t].w));
+    const T* xv = reinterpret_cast<const T*>(&raw[t]);
+    uint4 outv;
+    T* ov = reinterpret_cast<T*>(&outv);
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) {
+      float v = to_f32(xv[e]) * scale[e] + shift[e];
+      if (p.silu) v = silu_f(v);
+      ov[e] = from_f32<T>(v);
+    }
+    st16(dst + (long long)px * C, outv);
+  }
+}
+
+// Slice geometry of the one-launch GroupNorm: groups per slice (0: does not apply).
+struct GnOne {
+  int groups = 0, sv = 0, vpt = 0;
+};
+template <typename T> GnOne gn_one_geom(int HW, int C, int G) {
+  constexpr int VEC = Elem<T>::kVec;
+  const int cg = C / G;
+  for (int g = 1; g <= G && g <= kGnOneMaxGroups; g *= 2) {
+    if (G % g != 0) break;
+    const int ch = g * cg;
+    if (ch % VEC != 0 || (ch * (int)sizeof(T) < 32 && 2 * g <= G && 2 * g <= kGnOneMaxGroups)) continue;
+    const int sv = ch / VEC;
+    if (sv > 64) break;
+    const int pls = kGnOneThreads / sv, vpt = (HW + pls - 1) / pls;
+    // beyond 6 vectors per thread the few workgroups (groups x samples) take longer than the
+    // three launches over the whole chip (2 x 2304 x 640 bf16, 12: 17.2 us against 12.6),
+    // except where those walk (pixel, vector) pairs (2 x 1024 x 2560, 11: 14.9 against 20.0)
+    if (vpt > (C / VEC > 256 ? kGnOneMaxVec : 6)) break;
+    return GnOne{g, sv, vpt};
+  }
+  return GnOne{};
+}
+
+template <typename T, int VPT> void launch_gn_one(const GroupNormParams& p, const GnOne& o, int C, hipStream_t s) {
+  hipLaunchKernelGGL((gn_one_kernel<T, VPT>), dim3(p.G / o.groups, p.n), dim3(kGnOneThreads), 0, s, p, C, o.groups,
+                     o.sv);
+}
+
 constexpr int kLnMaxVec = 8;  // float4 vectors per lane: C <= 2048
 
 template <typename T> struct Store4;
@@ -456,6 +600,19 @@ template <typename T> void groupnorm(const GroupNormParams& p, hipStream_t s) {
   DN_CHECK(C % p.G == 0, "groupnorm: channels must divide into groups");
   DN_CHECK(p.c0 % VEC == 0 && p.c1 % VEC == 0, "groupnorm: channel counts must be multiples of 16 bytes");
   DN_CHECK(p.x0 && p.y && p.partial && p.stats && p.gamma && p.beta && (p.c1 == 0 || p.x1), "groupnorm: null");
+  const GnOne one = gn_one_geom<T>(p.HW, C, p.G);
+  if (one.groups) {
+    if (one.vpt <= 2)
+      launch_gn_one<T, 2>(p, one, C, s);
+    else if (one.vpt <= 4)
+      launch_gn_one<T, 4>(p, one, C, s);
+    else if (one.vpt <= 6)
+      launch_gn_one<T, 6>(p, one, C, s);
+    else
+      launch_gn_one<T, kGnOneMaxVec>(p, one, C, s);
+    DN_HIP(hipGetLastError());
+    return;
+  }
   const GnGeom g = gn_geom<T>(p.HW, C);
   hipLaunchKernelGGL(gn_partial_kernel<T>, dim3(g.chunks, p.n, g.vslices), dim3(256), 0, s, p, g);
   hipLaunchKernelGGL(gn_finalize_kernel, dim3(p.G, p.n), dim3(256), 0, s, p, g);
