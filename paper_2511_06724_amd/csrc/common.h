@@ -141,4 +141,35 @@ template <> struct Mma<float> {
 
 __device__ __forceinline__ int acc_row(int r, int lane) { return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); }
 
+// ---------------------------------------------------------------- direct-to-LDS loads
+
+typedef __attribute__((address_space(3))) void lds_void;
+
+// s_waitcnt immediate: vmcnt <= vm (bits 3:0 and 15:14), lgkmcnt <= 0 (bits 11:8),
+// expcnt unconstrained (bits 6:4 = 7).
+constexpr int wait_vm_lgkm0(int vm) { return (vm & 0xF) | (((vm >> 4) & 3) << 14) | (7 << 4); }
+
+// 16 bytes per lane global -> LDS (lane i writes lds + 16 i). Issued from inline
+// assembly: the compiler's wait insertion treats a global_load_lds it knows about as
+// making the vector-memory counter out of order and then drains every load
+// (vmcnt(0)) before the next use of any loaded register, which would serialise a
+// register prefetch with every LDS stage. The LDS data this writes is guarded by the
+// kernel's own waits and barriers (hand-overs, and a full drain before the LDS is reused
+// for something else); it writes no VGPRs. M0 holds the LDS address; nothing else in the
+// kernels that use it keeps a value in M0.
+__device__ __forceinline__ void dma16(const void* g, lds_void* lds) {
+  const unsigned a = static_cast<unsigned>(reinterpret_cast<__UINTPTR_TYPE__>(lds));
+  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "s"(a) : "memory", "m0");
+}
+
+// The same from a wave-uniform base and a 32-bit byte offset per lane.
+__device__ __forceinline__ void dma16_base(const void* base, unsigned off, lds_void* lds) {
+  const unsigned a = __builtin_amdgcn_readfirstlane(static_cast<unsigned>(reinterpret_cast<__UINTPTR_TYPE__>(lds)));
+  const unsigned long long b = reinterpret_cast<__UINTPTR_TYPE__>(base);
+  const unsigned long long u =
+      static_cast<unsigned long long>(__builtin_amdgcn_readfirstlane(static_cast<unsigned>(b >> 32))) << 32 |
+      static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<unsigned>(b)));
+  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(u), "s"(a) : "memory", "m0");
+}
+
 }  // namespace dn

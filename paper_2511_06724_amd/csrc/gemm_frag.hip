@@ -44,26 +44,6 @@ constexpr int kXcds = 8;
 constexpr int kBK = 64;
 constexpr int kRowBytes = 128;
 
-typedef __attribute__((address_space(3))) void lds_void;
-typedef __attribute__((address_space(1))) void gbl_void;
-
-// s_waitcnt immediate: vmcnt <= vm (bits 3:0 and 15:14), lgkmcnt <= 0 (bits 11:8),
-// expcnt unconstrained (bits 6:4 = 7).
-constexpr int wait_vm_lgkm0(int vm) { return (vm & 0xF) | (((vm >> 4) & 3) << 14) | (7 << 4); }
-
-// 16 bytes per lane global -> LDS (lane i writes lds + 16 i). Issued from inline
-// assembly: the compiler's wait insertion treats a global_load_lds it knows about as
-// making the vector-memory counter out of order and then drains every load
-// (vmcnt(0)) before the next use of any loaded register, which would serialise the
-// B-register prefetch with every A stage. The LDS data this writes is guarded by the
-// kernel's own waits and barriers (hand-overs, and a full drain before the epilogue);
-// it writes no VGPRs. M0 holds the LDS address; nothing else in these kernels keeps a
-// value in M0.
-__device__ __forceinline__ void dma16(const void* g, lds_void* lds) {
-  const unsigned a = static_cast<unsigned>(reinterpret_cast<__UINTPTR_TYPE__>(lds));
-  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(g), "s"(a) : "memory", "m0");
-}
-
 // Scheduling-group pattern of one k-step: NM MFMAs, each followed by one LDS read
 // (while the NR reads last) and by its share of the NV B loads.
 template <int I, int NM, int NR, int NV> struct KSched {

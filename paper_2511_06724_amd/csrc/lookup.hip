@@ -8,15 +8,12 @@
 // workgroup reduces the per-workgroup winners. Ties go to the lowest index at every
 // stage, so the result is the first maximum, independent of the launch shape.
 //
-// Batched search (up to 64 queries per pass): the scores of a 16-row tile against all
-// queries are one [16 x dim] x [dim x 64] contraction on the matrix cores
-// (v_mfma_f32_16x16x32_f16: fp16 operands, exact products, fp32 sums), so the table is
-// read from HBM once per 64 queries instead of once per query. Each lane loads its
-// A operand (row l % 16, 8 consecutive dims at 8 * (l / 16)) straight from the table:
-// one 16-byte load per 32-dim k-step, 64 contiguous bytes per row per instruction.
-// The queries sit in LDS in B-fragment order (one conflict-free 16-byte read per lane
-// and k-step). Row norms come from the same A registers (packed fp16 dot products),
-// and the top-1 per query is kept in registers while the wave walks its tiles.
+// Batched search (up to 64 queries per pass): the scores of 32-row tiles against all queries
+// are [32 x dim] x [dim x 64] contractions on the matrix cores (v_mfma_f32_32x32x16_f16: fp16
+// operands, exact products, fp32 sums), so the table is read from HBM once per 64 queries
+// instead of once per query. The queries stay in registers, the rows stream through LDS. Row
+// norms come from the same operands (packed fp16 dot products), and the top-1 per query is
+// kept in registers while a wave walks its tiles.
 #include "kernels.h"
 
 namespace dn {
@@ -243,136 +240,175 @@ __global__ __launch_bounds__(256) void reduce_kernel(const Cand* part, int nb, c
 
 // ---------------------------------------------------------------- batched search
 
-constexpr int kBatchQ = 64;          // queries per pass: 4 column tiles of 16
-constexpr int kBatchBlocks = 256;    // at most one workgroup per CU (the queries take up to 128 KB of LDS)
+constexpr int kBatchQ = 64;        // queries per pass: two 32-query halves
+constexpr int kBatchBlocks = 256;  // at most one workgroup per CU
+constexpr int kTileRows = 32;      // table rows per tile
+// dims per LDS stage; a tile takes at least two stages
+constexpr int stage_k(int dim) { return dim >= 512 ? 256 : 128; }
 
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
-// Two register sets of a tile's rows (4 KS VGPRs each) when they fit beside three
-// (KS = 8) or two waves per SIMD: the next tile's loads are then in flight while the
-// current tile is scored. dim 1024 keeps one set (two waves per SIMD).
-template <int KS> struct BatchCfg {
-  static constexpr bool kTwoSets = KS <= 24;
-  static constexpr int kWaves = KS <= 8 ? 12 : 8;
-};
+// dim = 16 KS. Two row groups of four waves share a workgroup. Wave (qh, kh) of a group holds
+// queries [32 qh, 32 qh + 32) over half kh of every stage's dims in registers (2 KS VGPRs: B
+// operands of the 32x32x16 f16 matrix-core step, lane l query l % 32, dims 16 s + 8 (l / 32)
+// ..), and the four waves score the group's 32-row tiles together: the kh = 1 halves of the
+// sums and norms reach the kh = 0 wave through LDS, which scores a tile one stage later. The
+// rows go global -> LDS in 512-byte (256 dims: 256-byte) pieces into a ring of R stages per group, swizzled
+// (16-byte chunk c of row r at position c ^ (r % 16)), so that the A operands are conflict-free
+// 16-byte LDS reads. A group's rows are contiguous; rows past its range read its last row and
+// are not scored.
+// Bound by HBM (the table once per 64 queries). The previous form loaded the A operands
+// straight from the table (64-byte pieces of 16 rows per load, half a line each) and re-read
+// every query operand from LDS per 16-row tile, which its loads did not hide: 48.0 us for
+// 100,000 x 768 against 39.2 us here; the table's own bound at the rate of a large copy
+// (5.0 TB/s) is 30 us.
+constexpr int kBatchGroups = 2, kBatchWaves = 4 * kBatchGroups;
+constexpr int kRingBytes = 64 * 1024;  // per group
 
-// dim = 32 * KS. q [nq][dim] (nq <= 64), cache [n][dim]; part [gridDim.x][64] receives
-// each workgroup's best (score, index) per query (queries >= nq score zero and are ignored).
 template <int KS>
-__global__ __launch_bounds__(BatchCfg<KS>::kWaves * 64) void scan_mfma_kernel(const uint16_t* q, int nq,
-                                                                            const uint16_t* cache, int n,
-                                                                            Cand* part) {
-  constexpr int NW = BatchCfg<KS>::kWaves;
-  constexpr int dim = 32 * KS;
-  extern __shared__ __align__(16) uint4 qf[];  // [4 column tiles][KS k-steps][64 lanes]
-  __shared__ Cand red[NW][kBatchQ];
-  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-  const int r16 = lane & 15, grp = lane >> 4;
-  for (int u = t; u < 4 * KS * 64; u += NW * 64) {
-    const int ln = u & 63, ks = (u >> 6) % KS, qt = (u >> 6) / KS;
-    const int qi = qt * 16 + (ln & 15);
-    qf[u] = qi < nq ? ld16(q + (long long)qi * dim + ks * 32 + 8 * (ln >> 4)) : make_uint4(0u, 0u, 0u, 0u);
+__global__ __launch_bounds__(kBatchWaves * 64) void scan_mfma_kernel(const uint16_t* q, int nq, const uint16_t* cache,
+                                                                     int n, Cand* part) {
+  constexpr int NG = kBatchGroups;
+  constexpr int dim = 16 * KS, SK = stage_k(dim), ST = dim / SK;  // stages per tile
+  constexpr int RB = 2 * SK;                                      // bytes of a row per stage
+  constexpr int SB = kTileRows * RB, R = kRingBytes / SB;         // bytes per stage, ring depth
+  constexpr int HS = SK / 32;                                     // k-steps per wave and stage
+  constexpr int CPR = RB / 16, RPI = 64 / CPR;                    // 16-byte chunks per row, rows per DMA
+  constexpr int NI = 8 / RPI;                                     // DMA instructions per wave and stage
+  static_assert(ST >= 2, "the partial sums of a tile are read before the next tile's are written");
+  extern __shared__ __align__(16) unsigned char ring[];  // [group][R][32 rows][RB]
+  __shared__ float half_acc[NG][2][16][64];
+  __shared__ float half_cc[NG][2][kTileRows];
+  __shared__ float inv[NG][2][kTileRows];
+  __shared__ Cand red[NG][kBatchQ];
+  const int t = threadIdx.x, lane = t & 63;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int grp = w >> 2, qh = w & 1, kh = (w >> 1) & 1;
+  const int r32 = lane & 31, h = lane >> 5;
+  // this group's rows [row0, row1): equal contiguous shares
+  const int shares = (int)gridDim.x * NG, per = n / shares + (n % shares != 0);
+  const long long begin = (long long)(blockIdx.x * NG + grp) * per;
+  const int row0 = (int)(begin < n ? begin : n), row1 = (int)(begin + per < n ? begin + per : n);
+  const int tiles = (per + kTileRows - 1) / kTileRows;  // the same for every group: barriers match
+  const int total = tiles * ST;
+
+  // DMA of stage g (tile g / ST, dims [SK (g % ST), + SK)): wave j of the group loads rows
+  // [8 j, 8 j + 8), RPI per instruction; stages past the end repeat the last one
+  unsigned char* const gring = ring + grp * kRingBytes;
+  const int drow = 8 * (w & 3) + lane / CPR;
+  const int last_row = row1 > 0 ? row1 - 1 : 0;
+  int dg = 0, dbase = row0 < last_row ? row0 : last_row, dst = 0;  // next stage, its tile's first row, its dims
+  auto issue = [&]() {
+    unsigned char* slot = gring + (dg % R) * SB;
+    const uint16_t* src = cache + (long long)dbase * dim + dst * SK;  // wave-uniform
+    const int lim = last_row - dbase;
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+      const int row = drow + RPI * j;
+      const unsigned off = (unsigned)min(row, lim) * (2 * dim) + (unsigned)(((lane % CPR) ^ (row & 15)) * 16);
+      dma16_base(src, off, (lds_void*)(slot + (8 * (w & 3) + RPI * j) * RB));
+    }
+    ++dg;
+    const bool more = dg < total, wrap = dst + 1 == ST;
+    dbase = more && wrap ? min(dbase + kTileRows, last_row) : dbase;
+    dst = more ? (wrap ? 0 : dst + 1) : dst;
+  };
+#pragma unroll
+  for (int s = 0; s < R - 1; ++s) issue();
+
+  f16x8 qf[ST * HS];
+  {
+    const int qi = 32 * qh + r32;
+    const uint16_t* qp = q + (long long)(qi < nq ? qi : 0) * dim + 16 * HS * kh + 8 * h;
+#pragma unroll
+    for (int s = 0; s < ST * HS; ++s)
+      qf[s] = *reinterpret_cast<const f16x8*>(qp + (s / HS) * SK + 16 * (s % HS));
+    // landed before the loop: waits for them inside it would drain the ring's DMA every tile
+#pragma unroll
+    for (int s = 0; s < ST * HS; ++s) asm volatile("" : "+v"(qf[s]));
   }
+
+  float best_s = -INFINITY;
+  int best_i = n;
+  // even and odd k-steps apart: half the length of the dependent chains
+  f32x16 acc[2], prev;
+  float cc[2] = {0.f, 0.f}, prev_cc = 0.f;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) acc[0][r] = acc[1][r] = prev[r] = 0.f;
+  // kh = 0: adds the other half of tile `tile` (in LDS) to prev and scores it
+  auto finish = [&](int tile) {
+    const float c2 = prev_cc + half_cc[grp][qh][r32];
+    inv[grp][qh][r32] = c2 > 0.f ? rsqrtf(c2) : -1.f;  // 1 / |c| of row r32, -1 for a zero row
+    const int base = tile * kTileRows;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      // c_row . q_(32 qh + r32), row = 8 (r / 4) + 4 h + r % 4: rows ascend with r
+      const int rr = 8 * (r >> 2) + 4 * h + (r & 3);
+      const float iv = inv[grp][qh][rr];
+      const float dot = prev[r] + half_acc[grp][qh][r][lane];
+      const float sc = iv > 0.f ? dot * iv : -INFINITY;
+      if (base + rr < row1 - row0 && sc > best_s) {
+        best_s = sc;
+        best_i = row0 + base + rr;
+      }
+    }
+  };
+  int g = 0;
+  for (int tile = 0; tile < tiles; ++tile) {
+#pragma unroll
+    for (int st = 0; st < ST; ++st, ++g) {
+      // this wave's DMA of stage g has landed (R - 2 later stages of NI loads follow it);
+      // after the barrier every wave's has, and every wave is done with stage g - 1, whose
+      // slot takes stage g + R - 1
+      __builtin_amdgcn_s_waitcnt(wait_vm_lgkm0((R - 2) * NI));
+      __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+      issue();
+      const unsigned char* slot = gring + (g % R) * SB + r32 * RB;
+#pragma unroll
+      for (int s = 0; s < HS; ++s) {
+        const f16x8 a = *reinterpret_cast<const f16x8*>(slot + (((2 * (HS * kh + s) + h) ^ (r32 & 15)) * 16));
+        acc[s & 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, qf[st * HS + s], acc[s & 1], 0, 0, 0);
+        const uint4 u = __builtin_bit_cast(uint4, a);
+        const unsigned wd[4] = {u.x, u.y, u.z, u.w};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) cc[k & 1] = __builtin_amdgcn_fdot2(as_h2(wd[k]), as_h2(wd[k]), cc[k & 1], false);
+      }
+      // the norm's terms are taken here (the compiler would sink them to the tile's end and
+      // keep every operand until then)
+      asm volatile("" : "+v"(cc[0]), "+v"(cc[1]));
+      if (st == 0 && kh == 0 && tile > 0) finish(tile - 1);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    prev = acc[0] + acc[1];
+    prev_cc = cc[0] + cc[1];
+    prev_cc += __shfl_xor(prev_cc, 32, 64);
+    if (kh == 1) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) half_acc[grp][qh][r][lane] = prev[r];
+      half_cc[grp][qh][r32] = prev_cc;
+    }
+    cc[0] = cc[1] = 0.f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[0][r] = acc[1][r] = 0.f;
+  }
+  __builtin_amdgcn_s_waitcnt(wait_vm_lgkm0(0));
   __syncthreads();
-  float best_s[4];
-  int best_i[4];
-#pragma unroll
-  for (int qt = 0; qt < 4; ++qt) {
-    best_s[qt] = -INFINITY;
-    best_i[qt] = n;
-  }
-  const int tiles = (n + 15) / 16;
-  const int stride = gridDim.x * NW;
-
-  // the lane's 16-byte slices of row tile * 16 + r16 (past the end: the last row, not scored);
-  // tile < tiles + 2 * stride keeps tile * 16 + 15 below 2^31 for n < 2^31 - 64
-  auto load = [&](uint4 (&a)[KS], int tile) {
-    const int row = tile * 16 + r16;
-    const uint16_t* src = cache + (long long)(row < n ? row : n - 1) * dim + 8 * grp;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) a[ks] = ld16(src + 32 * ks);
-  };
-  auto score = [&](const uint4 (&a)[KS], int tile) {
-    f32x4 acc[4];
-#pragma unroll
-    for (int qt = 0; qt < 4; ++qt) acc[qt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float cc = 0.f;
-    // opaque to the optimiser, so the query fragments are re-read from LDS per tile
-    // instead of being hoisted out of the loop into 16 KS registers
-    int ql = lane;
-    asm volatile("" : "+v"(ql));
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      const f16x8 av = __builtin_bit_cast(f16x8, a[ks]);
-#pragma unroll
-      for (int qt = 0; qt < 4; ++qt)
-        acc[qt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av, __builtin_bit_cast(f16x8, qf[(qt * KS + ks) * 64 + ql]),
-                                                         acc[qt], 0, 0, 0);
-      const unsigned wd[4] = {a[ks].x, a[ks].y, a[ks].z, a[ks].w};
-#pragma unroll
-      for (int k = 0; k < 4; ++k) cc = __builtin_amdgcn_fdot2(as_h2(wd[k]), as_h2(wd[k]), cc, false);
+  if (kh == 0) {
+    finish(tiles - 1);
+    // the two lane halves of a query
+    const float s2 = __shfl_xor(best_s, 32, 64);
+    const int i2 = __shfl_xor(best_i, 32, 64);
+    if (better(s2, i2, best_s, best_i)) {
+      best_s = s2;
+      best_i = i2;
     }
-    // |c|^2 of row r16: the four lane groups hold its four 8-dim slices of every k-step
-    cc += __shfl_xor(cc, 16, 64);
-    cc += __shfl_xor(cc, 32, 64);
-    // acc[qt][i] = c_(tile*16 + 4 grp + i) . q_(16 qt + r16)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int rr = 4 * grp + i;
-      const float c2 = __shfl(cc, rr, 64);
-      const int ri = tile * 16 + rr;
-      if (ri >= n) continue;
-#pragma unroll
-      for (int qt = 0; qt < 4; ++qt) {
-        const float sc = row_score(acc[qt][i], c2);
-        if (better(sc, ri, best_s[qt], best_i[qt])) {
-          best_s[qt] = sc;
-          best_i[qt] = ri;
-        }
-      }
-    }
-  };
-
-  const int first = blockIdx.x * NW + w;
-  if constexpr (BatchCfg<KS>::kTwoSets) {
-    // The look-ahead loads are unconditional (a tile past the end reads the last row,
-    // in bounds, and is never scored): inside a branch they would make the compiler's
-    // wait counts assume the worst case, so scoring a tile would wait for the next one.
-    uint4 a0[KS], a1[KS];
-    load(a0, first);
-    for (int tile = first; tile < tiles; tile += 2 * stride) {
-      const int t1 = tile + stride;
-      load(a1, t1);
-      score(a0, tile);
-      if (t1 >= tiles) break;
-      load(a0, t1 + stride);
-      score(a1, t1);
-    }
-  } else {
-    uint4 a0[KS];
-    for (int tile = first; tile < tiles; tile += stride) {
-      load(a0, tile);
-      score(a0, tile);
-    }
-  }
-  // the four lane groups of a query column, then the waves in order
-#pragma unroll
-  for (int qt = 0; qt < 4; ++qt) {
-#pragma unroll
-    for (int o = 16; o <= 32; o <<= 1) {
-      const float s2 = __shfl_xor(best_s[qt], o, 64);
-      const int i2 = __shfl_xor(best_i[qt], o, 64);
-      if (better(s2, i2, best_s[qt], best_i[qt])) {
-        best_s[qt] = s2;
-        best_i[qt] = i2;
-      }
-    }
-    if (grp == 0) red[w][qt * 16 + r16] = Cand{best_s[qt], best_i[qt]};
+    if (h == 0) red[grp][32 * qh + r32] = Cand{best_s, best_i};
   }
   __syncthreads();
   if (t < kBatchQ) {
     Cand b = red[0][t];
-    for (int k = 1; k < NW; ++k)
+    for (int k = 1; k < NG; ++k)
       if (better(red[k][t].s, red[k][t].i, b.s, b.i)) b = red[k][t];
     part[(long long)blockIdx.x * kBatchQ + t] = b;
   }
@@ -426,20 +462,21 @@ __global__ __launch_bounds__(256) void reduce_batch_kernel(const Cand* part, int
   }
 }
 
-// Launches the scan over min(256, tiles / waves) workgroups; returns that count.
+// Launches the scan over at most 256 workgroups, each group with at least a tile's rows where
+// the table has them; returns that count.
 template <int KS>
 int launch_batch(const uint16_t* q, int nq, const uint16_t* cache, int n, Cand* part, hipStream_t s) {
-  constexpr int NW = BatchCfg<KS>::kWaves;
-  const long long want = ((n + 15) / 16 + NW - 1) / NW;
-  const int nb = static_cast<int>(want < kBatchBlocks ? want : kBatchBlocks);
-  const size_t lds = sizeof(uint4) * 4 * KS * 64;
+  const int rows = kTileRows * kBatchGroups;
+  const int want = n / rows + (n % rows != 0);
+  const int nb = want < kBatchBlocks ? want : kBatchBlocks;
+  const size_t lds = (size_t)kBatchGroups * kRingBytes;
   static bool attr = false;  // per process: the attribute belongs to the code object
   if (!attr) {
     DN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&scan_mfma_kernel<KS>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)));
     attr = true;
   }
-  hipLaunchKernelGGL(scan_mfma_kernel<KS>, dim3(nb), dim3(NW * 64), lds, s, q, nq, cache, n, part);
+  hipLaunchKernelGGL(scan_mfma_kernel<KS>, dim3(nb), dim3(kBatchWaves * 64), lds, s, q, nq, cache, n, part);
   return nb;
 }
 
@@ -499,10 +536,10 @@ void lookup_batch(const uint16_t* q, int nq, const uint16_t* cache, long long n,
   Cand* part = static_cast<Cand*>(ws);
   int nb = 0;
   switch (dim) {
-    case 256: nb = launch_batch<8>(q, nq, cache, n32, part, s); break;
-    case 512: nb = launch_batch<16>(q, nq, cache, n32, part, s); break;
-    case 768: nb = launch_batch<24>(q, nq, cache, n32, part, s); break;
-    default: nb = launch_batch<32>(q, nq, cache, n32, part, s); break;
+    case 256: nb = launch_batch<16>(q, nq, cache, n32, part, s); break;
+    case 512: nb = launch_batch<32>(q, nq, cache, n32, part, s); break;
+    case 768: nb = launch_batch<48>(q, nq, cache, n32, part, s); break;
+    default: nb = launch_batch<64>(q, nq, cache, n32, part, s); break;
   }
   const KTable tab = kt ? *kt : KTable();
   hipLaunchKernelGGL(reduce_batch_kernel, dim3(nq), dim3(256), 0, s, part, nb, q, dim, idx_out, score_out, tab,
