@@ -426,9 +426,9 @@ __global__ __launch_bounds__(64 * NQ) __attribute__((amdgpu_waves_per_eu(WPE, WP
       mc[j] = fmaxf(m, sa[1][4 * j + 3]);
     }
     float mx = fmaxf(fmaxf(mc[0], mc[1]), fmaxf(mc[2], mc[3]));
-    mx = fmaxf(mx, partner(mx)) + m_fold;
-    if (__any(mx > m_ref + kLazy)) {
-      const float m_new = fmaxf(m_ref, mx);
+    mx += m_fold;
+    if (__any(mx > m_ref + kLazy)) {  // either half of a query's keys: they exchange maxima only here
+      const float m_new = fmaxf(m_ref, fmaxf(mx, partner(mx)));
       const float alpha = fast_exp2(m_ref - m_new);
       l_run *= alpha;
 #pragma unroll
@@ -464,8 +464,7 @@ __global__ __launch_bounds__(64 * NQ) __attribute__((amdgpu_waves_per_eu(WPE, WP
           sp[e & 1] = __builtin_amdgcn_fdot2_f32_bf16(pair, ones, sp[e & 1], false);
         }
       }
-    const float rs = sp[0] + sp[1];
-    l_run += rs + partner(rs);
+    l_run += sp[0] + sp[1];
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -529,6 +528,7 @@ __global__ __launch_bounds__(64 * NQ) __attribute__((amdgpu_waves_per_eu(WPE, WP
   }
   __builtin_amdgcn_s_waitcnt(attn_wait_vm_lgkm0(0));
 
+  l_run += partner(l_run);  // each half has summed its own keys
   const int qi = q0 + (lane & 31);
   if (qi < p.Sq) {
     const float inv = 1.f / l_run;
@@ -579,19 +579,27 @@ template <typename T> void attention(const AttnParams& p, int D, hipStream_t s) 
   constexpr int VEC = 16 / sizeof(T);
   DN_CHECK(p.ldq % VEC == 0 && p.ldk % VEC == 0 && p.vt_ld % VEC == 0, "attention: strides must be 16-byte multiples");
   DN_CHECK(p.vt_ld >= (p.Skv + kKT - 1) / kKT * kKT, "attention: V^T rows must cover whole 64-key tiles");
-  // bf16, head dim 64: the software-pipelined kernel. Long key ranges (self-attention)
-  // use a ring of 3 key tiles; long query ranges: 4 x 32 queries per workgroup at three
-  // waves per SIMD without score read-ahead, otherwise 2 x 32 queries with read-ahead.
-  // Short key ranges (cross-attention over the 77 text tokens) use a ring of 2 tiles,
-  // 4 x 32 queries, three waves per SIMD (the fastest measured shapes for 4096 and
-  // 1024 tokens). fp32 and head dim 32 take the register-staged kernel below.
+  // bf16, head dim 64: the software-pipelined kernel. Four waves (128 queries) per workgroup
+  // share a key tile; the variant follows from how many such workgroups a CU gets, since the
+  // CU with one more sets the time (measured, us, in the order below):
+  //  - up to one: two waves per SIMD's registers (2 x 20 heads, 576 keys 10.1, three waves per
+  //    SIMD 10.2, two-wave workgroups with score read-ahead 12.0; 2 x 10, 1024: 14.5, 15.0, 17.7);
+  //  - up to 1.6: two-wave workgroups with read-ahead halve the uneven part (2 x 10, 1600: 28.2,
+  //    29.2, 25.5; 2 x 20, 1024: 20.5, 21.1, 19.3);
+  //  - up to two: as up to one (2 x 8, 4096: 74.2, 76.3, 105.9);
+  //  - more: three waves per SIMD (2 x 10, 4096: 110.2, 102.1, 148.3; 4 x 20, 1024: 33.5, 30.7, 38.3).
+  // Rings of three key tiles instead of two were no faster without read-ahead (107.9, 32.1).
+  // Short key ranges (the 77 text tokens) take three waves per SIMD (2 x 10, 4096 queries: 11.9,
+  // 10.1, 13.1). fp32 and head dim 32 take the register-staged kernel below.
   if (sizeof(T) == 2 && D == 64) {
-    if (p.Skv < 256)
+    constexpr int kCus = 256;
+    const long long wgs = (long long)((p.Sq + 127) / 128) * p.heads * p.B;
+    if (p.Skv < 256 || wgs > 2 * kCus)
       launch_pipe<4, 2, 3, false>(p, s);
-    else if (p.Sq >= 2048)
-      launch_pipe<4, 3, 3, false>(p, s);
-    else
+    else if (wgs > kCus && 10 * wgs <= 16 * kCus)
       launch_pipe<2, 3, 2, true>(p, s);
+    else
+      launch_pipe<4, 2, 2, false>(p, s);
     DN_HIP(hipGetLastError());
     return;
   }

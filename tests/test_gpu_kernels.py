@@ -235,6 +235,14 @@ def test_attention(dtype, B, heads, Sq, Skv, d):
         assert np.all(got[..., d:dp] == 0)
 
 
+@pytest.mark.parametrize("B,heads,Sq,Skv", [(2, 20, 300, 260), (5, 17, 385, 256), (6, 20, 300, 260), (8, 17, 385, 257),
+                                            (8, 20, 300, 260), (9, 20, 300, 321)])
+def test_attention_variants(B, heads, Sq, Skv):
+    """The bf16 head-dim-64 kernel's variants (up to one, 1.6, two and more than two 128-query
+    workgroups per CU), with ragged query and key tails."""
+    test_attention(dn.DN_BF16, B, heads, Sq, Skv, 64)
+
+
 @pytest.mark.parametrize("dtype", DT)
 @pytest.mark.parametrize("M,seq,heads,dp,K", [(300, 150, 3, 64, 128), (512, 256, 4, 32, 64), (8192, 4096, 10, 64, 640),
                                               (2048, 1024, 20, 64, 1280)])
