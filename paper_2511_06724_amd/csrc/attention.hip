@@ -231,6 +231,130 @@ __global__ __launch_bounds__(64 * NW) void attn_kernel(AttnParams p) {
 }
 
 // ---------------------------------------------------------------------------
+// Few queries: eight waves split the keys of 32 queries. A workgroup of attn_kernel walks all
+// key tiles alone (2 x 4 heads, 256 x 256, head dim 32, fp32: 32 workgroups, 12.0 us); here
+// each wave takes every eighth 32-key tile straight from global memory, keeps its own
+// reference maximum, and the partial (m, l, O) meet in LDS in wave order (deterministic;
+// 4.7 us). fp32 operands are read as in the wave-split GEMM: four consecutive head dims (K, Q)
+// or keys (V^T) per lane, the same k order for both operands of an MFMA.
+constexpr int kKsWaves = 8;
+
+template <typename T, int D>
+__global__ __launch_bounds__(64 * kKsWaves) void attn_keysplit_kernel(AttnParams p) {
+  using MM = Mma<T>;
+  constexpr int DB = D / 32;
+  constexpr int NV = D / (sizeof(T) == 4 ? 8 : 16);  // 16-byte operands of a K or Q row per lane
+  __shared__ float sm[kKsWaves][32], sl[kKsWaves][32];
+  extern __shared__ __align__(16) unsigned char attn_smem[];
+  float* so = reinterpret_cast<float*>(attn_smem);  // [wave][DB][16][64]
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int half = lane >> 5, r32 = lane & 31;
+  const int b = blockIdx.z, h = blockIdx.y, q0 = blockIdx.x * 32;
+  constexpr int VEC = 16 / sizeof(T);
+  const T* qp = static_cast<const T*>(p.q) + b * p.q_bs + h * D + half * VEC;
+  const T* kp = static_cast<const T*>(p.k) + b * p.k_bs + h * D + half * VEC;
+  const T* vtp = static_cast<const T*>(p.vt) + ((long long)b * p.heads + h) * D * p.vt_ld;
+  uint4 qv[NV];
+#pragma unroll
+  for (int s = 0; s < NV; ++s) qv[s] = ld16(qp + (long long)min(q0 + r32, p.Sq - 1) * p.ldq + s * 2 * VEC);
+  f32x16 o[DB];
+#pragma unroll
+  for (int d = 0; d < DB; ++d)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) o[d][r] = 0.f;
+  float m_ref = -INFINITY, l_run = 0.f;
+  for (int k0 = wave * 32; k0 < p.Skv; k0 += 32 * kKsWaves) {
+    uint4 kv[NV];
+    const T* kr = kp + (long long)min(k0 + r32, p.Skv - 1) * p.ldk;
+#pragma unroll
+    for (int s = 0; s < NV; ++s) kv[s] = ld16(kr + s * 2 * VEC);
+    f32x16 sa;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) sa[r] = 0.f;
+#pragma unroll
+    for (int s = 0; s < NV; ++s) {
+      if constexpr (sizeof(T) == 4) {
+        const f32x4 ka = __builtin_bit_cast(f32x4, kv[s]), qa = __builtin_bit_cast(f32x4, qv[s]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sa = MM::mma(ka[e], qa[e], sa);
+      } else {
+        sa = MM::mma(__builtin_bit_cast(bf16x8, kv[s]), __builtin_bit_cast(bf16x8, qv[s]), sa);
+      }
+    }
+    if (k0 + 32 > p.Skv) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if (k0 + acc_row(r, lane) >= p.Skv) sa[r] = -INFINITY;
+    }
+    float mx = sa[0];
+#pragma unroll
+    for (int r = 1; r < 16; ++r) mx = fmaxf(mx, sa[r]);
+    mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * p.scale_log2;
+    const float m_new = fmaxf(m_ref, mx);
+    const float alpha = fast_exp2(m_ref - m_new);
+    float rs = 0.f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      sa[r] = fast_exp2(sa[r] * p.scale_log2 - m_new);
+      rs += sa[r];
+    }
+    l_run = l_run * alpha + rs + __shfl_xor(rs, 32, 64);
+    m_ref = m_new;
+#pragma unroll
+    for (int d = 0; d < DB; ++d) {
+      const T* vr = vtp + (long long)(d * 32 + r32) * p.vt_ld + k0;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[d][r] *= alpha;
+      if constexpr (sizeof(T) == 4) {
+        // register 4 g + e: key 8 g + 4 half + e
+        f32x4 vv[4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) vv[g] = *reinterpret_cast<const f32x4*>(vr + 8 * g + 4 * half);
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[d] = MM::mma(vv[g][e], sa[4 * g + e], o[d]);
+      } else {
+#pragma unroll
+        for (int c = 0; c < 2; ++c) o[d] = MM::mma(PvFrag<T>::v(vr, 0, c, half), PvFrag<T>::p(sa, c), o[d]);
+      }
+    }
+  }
+#pragma unroll
+  for (int d = 0; d < DB; ++d)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) so[((wave * DB + d) * 16 + r) * 64 + lane] = o[d][r];
+  if (half == 0) {
+    sm[wave][r32] = m_ref;
+    sl[wave][r32] = l_run;
+  }
+  __syncthreads();
+  // thread: head dims 32 d + 8 g + 4 half .. + 3 of query r32; waves that had no keys hold
+  // m = -inf and weigh nothing
+  const int qi = q0 + r32;
+  for (int u = threadIdx.x >> 6; u < 4 * DB; u += kKsWaves) {
+    const int d = u >> 2, g = u & 3;
+    float m = sm[0][r32];
+#pragma unroll
+    for (int w = 1; w < kKsWaves; ++w) m = fmaxf(m, sm[w][r32]);
+    float l = 0.f, v[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < kKsWaves; ++w) {
+      const float f = fast_exp2(sm[w][r32] - m);
+      l += f * sl[w][r32];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] += f * so[((w * DB + d) * 16 + 4 * g + e) * 64 + lane];
+    }
+    if (qi >= p.Sq) continue;
+    const float inv = 1.f / l;
+    T* dst = static_cast<T*>(p.o) + b * p.o_bs + (long long)qi * p.ldo + h * D + d * 32 + 8 * g + 4 * half;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) dst[e] = from_f32<T>(v[e] * inv);
+  }
+}
+
+// ---------------------------------------------------------------------------
 // bf16, head dim 64: software-pipelined kernel for long key ranges.
 //
 // Same math as attn_kernel. A workgroup covers NQ x 32 queries of one (sample,
@@ -558,6 +682,17 @@ template <int NQ, int R, int WPE, bool PIPE> void launch_pipe(const AttnParams& 
                      qtiles);
 }
 
+template <typename T, int D> void launch_keysplit(const AttnParams& p, hipStream_t s) {
+  constexpr size_t lds = sizeof(float) * kKsWaves * (D / 32) * 16 * 64;
+  static bool attr_set = false;
+  if (!attr_set) {
+    DN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_keysplit_kernel<T, D>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)));
+    attr_set = true;
+  }
+  hipLaunchKernelGGL((attn_keysplit_kernel<T, D>), dim3((p.Sq + 31) / 32, p.heads, p.B), dim3(64 * kKsWaves), lds, s, p);
+}
+
 template <typename T, int D, int NW> void launch(dim3 grid, const AttnParams& p, hipStream_t s) {
   constexpr int VEC = 16 / sizeof(T);
   const size_t lds = size_t(2) * (kKT * (D + VEC) + D * (kKT + VEC)) * sizeof(T);
@@ -600,6 +735,15 @@ template <typename T> void attention(const AttnParams& p, int D, hipStream_t s) 
       launch_pipe<2, 3, 2, true>(p, s);
     else
       launch_pipe<4, 2, 2, false>(p, s);
+    DN_HIP(hipGetLastError());
+    return;
+  }
+  // fp32 and head dim 32 with fewer 64-query workgroups than CUs: the keys split over waves
+  if ((long long)((p.Sq + 63) / 64) * p.heads * p.B < 256) {
+    if (D == 32)
+      launch_keysplit<T, 32>(p, s);
+    else if constexpr (sizeof(T) == 4)  // (bf16 with head dim 64 has returned)
+      launch_keysplit<T, 64>(p, s);
     DN_HIP(hipGetLastError());
     return;
   }

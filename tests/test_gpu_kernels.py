@@ -235,6 +235,15 @@ def test_attention(dtype, B, heads, Sq, Skv, d):
         assert np.all(got[..., d:dp] == 0)
 
 
+@pytest.mark.parametrize("dtype", DT)
+@pytest.mark.parametrize("B,heads,Sq,Skv,d", [(1, 1, 1, 31, 16), (1, 2, 33, 33, 32), (2, 4, 64, 256, 16), (1, 3, 95, 513, 32),
+                                              (1, 1, 40, 300, 64), (2, 64, 128, 70, 32)])
+def test_attention_few_queries(dtype, B, heads, Sq, Skv, d):
+    """Keys split over the waves (fp32, and bf16 with head dims up to 32): fewer key tiles than
+    waves, uneven shares, ragged last tile; the last case has enough workgroups not to."""
+    test_attention(dtype, B, heads, Sq, Skv, d)
+
+
 @pytest.mark.parametrize("B,heads,Sq,Skv", [(2, 20, 300, 260), (5, 17, 385, 256), (6, 20, 300, 260), (8, 17, 385, 257),
                                             (8, 20, 300, 260), (9, 20, 300, 321)])
 def test_attention_variants(B, heads, Sq, Skv):
