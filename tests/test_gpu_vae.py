@@ -46,6 +46,20 @@ def test_tiny_decoder_fp32(batch):
     assert e <= 1e-4
 
 
+@pytest.mark.parametrize("h,w", [(24, 40), (8, 264), (72, 120), (16, 1040)])
+def test_tiny_decoder_fp32_attention_lengths(h, w):
+    """Middle-block attention over 960, 2112, 8640 and 16640 positions: every row length class
+    of the softmax (rows in registers), none of them a full one."""
+    announce(f"vae tiny fp32 latent {h}x{w}")
+    cfg = W.tiny_vae(W.DN_FP32).with_(latent_h=h, latent_w=w)
+    blob = W.weight_blob(dn.vae_weight_table(cfg), 31)
+    z = W.normal((1, 4, h, w), 32)
+    got = _decode(cfg, blob, z)[0]
+    e = rel_l2(got, OV.decode(cfg, OV.unpack(cfg, blob), z))
+    announce(f"  rel-L2 {e:.3e}")
+    assert e <= 1e-4
+
+
 def _bf16_case(cfg, seed, blob=None):
     blob = W.weight_blob(dn.vae_weight_table(cfg), seed) if blob is None else blob
     z = W.normal((cfg.batch, cfg.latent_c, cfg.latent_h, cfg.latent_w), seed + 1)
