@@ -6,9 +6,12 @@
 
 namespace dn {
 
+// also compiled for the host, where the tests run it
+#define DN_HD __host__ __device__
+
 template <typename T> struct OutVec;
 template <> struct OutVec<bf16> {
-  __device__ static __forceinline__ void store(bf16* p, const float v[4]) {
+  DN_HD static __forceinline__ void store(bf16* p, const float v[4]) {
     bf16x4 o;
     o[0] = static_cast<bf16>(v[0]);
     o[1] = static_cast<bf16>(v[1]);
@@ -16,7 +19,7 @@ template <> struct OutVec<bf16> {
     o[3] = static_cast<bf16>(v[3]);
     *reinterpret_cast<bf16x4*>(p) = o;
   }
-  __device__ static __forceinline__ void load(const bf16* p, float v[4]) {
+  DN_HD static __forceinline__ void load(const bf16* p, float v[4]) {
     const bf16x4 i = *reinterpret_cast<const bf16x4*>(p);
     v[0] = static_cast<float>(i[0]);
     v[1] = static_cast<float>(i[1]);
@@ -25,10 +28,10 @@ template <> struct OutVec<bf16> {
   }
 };
 template <> struct OutVec<float> {
-  __device__ static __forceinline__ void store(float* p, const float v[4]) {
+  DN_HD static __forceinline__ void store(float* p, const float v[4]) {
     *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
   }
-  __device__ static __forceinline__ void load(const float* p, float v[4]) {
+  DN_HD static __forceinline__ void load(const float* p, float v[4]) {
     const float4 i = *reinterpret_cast<const float4*>(p);
     v[0] = i.x;
     v[1] = i.y;
@@ -37,12 +40,18 @@ template <> struct OutVec<float> {
   }
 };
 
-// Stores 4 consecutive output columns [n, n + 4) of row m (n % 4 == 0), masking
-// columns >= n_store element-wise when the group straddles the edge.
+// Whether four consecutive elements (16 bytes of fp32, 8 of bf16) at columns that are multiples
+// of 4 can be one access: the row stride and the base must both be multiples of their size.
+DN_HD __forceinline__ bool vec4_ok(const void* base, int ld, int elem_bytes) {
+  return ((reinterpret_cast<__UINTPTR_TYPE__>(base) | (__UINTPTR_TYPE__)ld * elem_bytes) & (4 * elem_bytes - 1)) == 0;
+}
+
+// Stores 4 consecutive output columns [n, n + 4) of row m (n % 4 == 0), element-wise where
+// the group straddles n_store (columns past it are masked) or the layout is not aligned.
 template <typename T>
-__device__ __forceinline__ void store4(const GemmParams& p, int m, int n, const float v[4], int n_store) {
+DN_HD __forceinline__ void store4(const GemmParams& p, int m, int n, const float v[4], int n_store) {
   const long long o = (long long)m * p.ldo + n;
-  const bool vec = n + 4 <= n_store && (p.ldo & 3) == 0;
+  const bool vec = n + 4 <= n_store && vec4_ok(p.out, p.ldo, p.out_f32 ? 4 : (int)sizeof(T));
   if (p.out_f32) {
     float* out = static_cast<float*>(p.out);
     if (vec) {
@@ -65,7 +74,7 @@ __device__ __forceinline__ void store4(const GemmParams& p, int m, int n, const 
 // v holds acc[m][n .. n + 3]: adds bias, the per-sample row vector and the
 // residual, then stores; columns >= vt_col0 go to the transposed V buffer
 // vt[sample][head][d][token] (row stride vt_ld) instead of `out`.
-template <typename T> __device__ __forceinline__ void epilogue_group(const GemmParams& p, int m, int n, float v[4]) {
+template <typename T> DN_HD __forceinline__ void epilogue_group(const GemmParams& p, int m, int n, float v[4]) {
   if (n >= p.n_store) return;
   const bool full = n + 4 <= p.n_store;
   if (p.bias)
@@ -76,7 +85,7 @@ template <typename T> __device__ __forceinline__ void epilogue_group(const GemmP
   }
   if (p.resid) {
     const long long ro = (long long)m * p.ldr + n;
-    if (full && (p.ldr & 3) == 0) {
+    if (full && vec4_ok(p.resid, p.ldr, p.resid_f32 ? 4 : (int)sizeof(T))) {
       float r[4];
       if (p.resid_f32)
         OutVec<float>::load(static_cast<const float*>(p.resid) + ro, r);

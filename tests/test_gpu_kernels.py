@@ -74,8 +74,8 @@ def test_linear(dtype, M, N, K):
 def test_linear_epilogue_forms(M, N, K, off):
     """The GEMM epilogue's output kinds and their layouts (bf16): bf16 and fp32 outputs with a
     residual of either type, ragged rows and column tails of every tile; with off elements of
-    offset on bias, residual and output none of them is 16-byte aligned (the element-wise
-    form). Bound: fp32 outputs differ from exact sums by fp32 rounding (1e-5), bf16 outputs by
+    offset on bias, residual and output none of them is 16-byte aligned (the form that goes
+    through LDS, whose accesses are as wide as each base allows). Bound: fp32 outputs differ from exact sums by fp32 rounding (1e-5), bf16 outputs by
     one rounding (2^-9 relative, below TOL)."""
     announce(f"epilogue forms M={M} N={N} K={K} off={off}")
     r = _rng(M + N + K + off)
