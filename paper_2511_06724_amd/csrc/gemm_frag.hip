@@ -79,8 +79,7 @@ __device__ __forceinline__ bool aligned16(const void* q) {
 // 2048 x 3840 x 1280 32.3 -> 28.2 us, projection 2048 x 1280 x 1280 with an fp32 residual
 // 20.1 -> 17.8 us, FF-in 66.6 -> 63.1 us, 32768-row convolution 320 -> 320 77.9 -> 72.7 us.
 // Layouts the vector forms do not take (bases or leading dimensions that are not 16-byte
-// aligned, a V^T split inside a 32-column block or an odd sequence) go through LDS in a
-// rolled loop.
+// aligned) go through LDS in a rolled loop.
 
 // kinds of the vector path
 enum EpiKind { kEpiGeneric = 0, kEpiBf16, kEpiF32, kEpiGeglu };
@@ -95,11 +94,18 @@ __device__ __forceinline__ int epi_kind(const GemmParams& p) {
   if (p.out_fp8) return kEpiGeneric;
   if (p.rowvec && (p.rowvec_ld % 4 != 0 || !aligned16(p.rowvec))) return kEpiGeneric;
   if (p.resid && (!aligned16(p.resid) || p.ldr % 8 != 0)) return kEpiGeneric;
-  if (p.vt && (p.vt_col0 % 32 != 0 || p.vt_dp % 32 != 0 || p.vt_seq % 2 != 0 || p.vt_ld % 2 != 0 || p.out_f32 ||
-               p.rowvec || p.resid || (reinterpret_cast<__UINTPTR_TYPE__>(p.vt) & 3) != 0))
-    return kEpiGeneric;
+  if (p.vt && (p.out_f32 || p.rowvec || p.resid)) return kEpiGeneric;
   if (p.out_f32) return p.ldo % 4 == 0 ? kEpiF32 : kEpiGeneric;
   return p.ldo % 8 == 0 ? kEpiBf16 : kEpiGeneric;
+}
+
+// V^T columns of the kEpiBf16 kind as 4-byte token pairs: every sample starts at an even row
+// and an even, 4-byte aligned address. Otherwise (odd token counts: 77 text tokens, 25 x 21
+// grids) those blocks, and only those, store 2-byte tokens: 25.4 us at 1922 x 3840 x 1280 (961
+// tokens a sample), where the whole launch through LDS took 35.8; the 77-token context
+// 308 x 1280 x 768 7.4 against 9.5.
+__device__ __forceinline__ bool vt_pairs(const GemmParams& p) {
+  return p.vt_col0 % 32 == 0 && p.vt_seq % 2 == 0 && p.vt_ld % 2 == 0 && (reinterpret_cast<__UINTPTR_TYPE__>(p.vt) & 3) == 0;
 }
 
 __device__ __forceinline__ f32x4 ld_f4(const float* q) { return *reinterpret_cast<const f32x4*>(q); }
@@ -432,23 +438,39 @@ __device__ __forceinline__ void wave_epilogue(const GemmParams& p, const f32x16 
         float v[4][4];
 #pragma unroll
         for (int g = 0; g < 4; ++g) biased(acc[i][j], n, g, bias[j][g], v[g]);
-        if (p.vt && n >= p.vt_col0) {
-          // rows are tokens: neighbouring lanes exchange one of two columns, so a lane
-          // stores two consecutive tokens of a column (4 bytes; 64-byte segments)
-          const int nn = n - p.vt_col0, h = nn / p.vt_dp, d = nn - h * p.vt_dp;
-          const bool odd = lane & 1;
+        if (p.vt && n + 32 > p.vt_col0) {
+          // rows are tokens; column nn of V^T is row nn of the sample's heads x dp
           bf16* dst = static_cast<bf16*>(p.vt) +
-                      (((long long)vb * p.vt_heads + h) * p.vt_dp + d + h4 + (odd ? 1 : 0)) * p.vt_ld + (vs & ~1);
-          const unsigned sel = odd ? 0x03020706u : 0x05040100u;
+                      ((long long)vb * p.vt_heads * p.vt_dp + n - p.vt_col0 + h4) * p.vt_ld + vs;
+          if (vt_pairs(p)) {
+            // neighbouring lanes exchange one of two columns, so a lane stores two
+            // consecutive tokens of a column (4 bytes; 64-byte segments)
+            const bool odd = lane & 1;
+            if (odd) dst += p.vt_ld - 1;
+            const unsigned sel = odd ? 0x03020706u : 0x05040100u;
 #pragma unroll
-          for (int g = 0; g < 4; ++g)
+            for (int g = 0; g < 4; ++g)
 #pragma unroll
-            for (int e = 0; e < 4; e += 2) {
-              const unsigned x = pack_bf16(v[g][e], v[g][e + 1]);
-              const unsigned y = __builtin_amdgcn_update_dpp(0u, x, 0xb1, 0xf, 0xf, true);  // lane ^ 1
-              const unsigned w = __builtin_amdgcn_perm(y, x, sel);
-              if (m < p.M) *reinterpret_cast<unsigned*>(dst + (long long)(8 * g + e) * p.vt_ld) = w;
+              for (int e = 0; e < 4; e += 2) {
+                const unsigned x = pack_bf16(v[g][e], v[g][e + 1]);
+                const unsigned y = __builtin_amdgcn_update_dpp(0u, x, 0xb1, 0xf, 0xf, true);  // lane ^ 1
+                const unsigned w = __builtin_amdgcn_perm(y, x, sel);
+                if (m < p.M) *reinterpret_cast<unsigned*>(dst + (long long)(8 * g + e) * p.vt_ld) = w;
+              }
+          } else if (m < p.M) {
+            // one token per lane: lanes 0 - 31 and 32 - 63 store 32 consecutive tokens of a
+            // column each; in a block that straddles the split, columns before it to out
+            bf16* out = static_cast<bf16*>(p.out) + (long long)m * p.ldo + n + h4;
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+              if (n + 8 * g + h4 >= p.vt_col0) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) dst[(long long)(8 * g + e) * p.vt_ld] = static_cast<bf16>(v[g][e]);
+              } else {
+                OutVec<bf16>::store(out + 8 * g, v[g]);
+              }
             }
+          }
           continue;
         }
         if (rv)

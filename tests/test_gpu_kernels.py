@@ -254,11 +254,13 @@ def test_attention_variants(B, heads, Sq, Skv):
 
 @pytest.mark.parametrize("dtype", DT)
 @pytest.mark.parametrize("M,seq,heads,dp,K", [(300, 150, 3, 64, 128), (512, 256, 4, 32, 64), (8192, 4096, 10, 64, 640),
-                                              (2048, 1024, 20, 64, 1280)])
+                                              (2048, 1024, 20, 64, 1280), (154, 77, 20, 64, 128), (578, 289, 10, 64, 640),
+                                              (1922, 961, 20, 64, 256), (2178, 1089, 8, 64, 320), (3, 1, 3, 32, 64)])
 def test_linear_vt(dtype, M, seq, heads, dp, K):
     """Attention input projection: Q, K columns to y, V columns transposed per head
-    into vt[sample][head][d][token] (the last two shapes are the SD-XL QKV projections
-    at the 64x64 and 32x32 levels, on the fragment-B kernel)."""
+    into vt[sample][head][d][token] (8192 and 2048 rows are the SD-XL QKV projections
+    at the 64x64 and 32x32 levels, on the fragment-B kernel). Odd token counts (V^T tokens
+    stored one by one): the 77 text tokens, 17 x 17, 31 x 31 and 33 x 33 grids, one token."""
     announce(f"linear_vt dtype={dtype} M={M} seq={seq} heads={heads} dp={dp} K={K}")
     P = heads * dp
     N = 3 * P
@@ -277,6 +279,31 @@ def test_linear_vt(dtype, M, seq, heads, dp, K):
     got = host(vt)
     assert rel_l2(got[..., :seq], ref_vt) < TOL[dtype]
     assert np.all(got[..., seq:] == 0)
+
+
+@pytest.mark.parametrize("dtype", DT)
+@pytest.mark.parametrize("M,seq,N,col0,heads,dp,K", [(66, 33, 96, 40, 7, 8, 64), (64, 32, 96, 40, 7, 8, 64),
+                                                     (300, 150, 160, 56, 26, 4, 128), (75, 25, 96, 36, 3, 20, 64),
+                                                     (400, 200, 128, 32, 2, 48, 64), (260, 130, 64, 24, 2, 20, 64)])
+def test_linear_vt_splits(dtype, M, seq, N, col0, heads, dp, K):
+    """The V^T columns starting inside a 32-column block, or at leading dimensions of the other
+    outputs that are (40, 56, 24) and are not (36) whole 16-byte vectors, at odd and even
+    token counts; V^T rows of an odd length (seq + 1 or seq). Same bound as test_linear_vt."""
+    announce(f"linear_vt split dtype={dtype} M={M} seq={seq} N={N} col0={col0} heads={heads} dp={dp}")
+    r = _rng(M + N + col0)
+    x, xh = to_dev(r.standard_normal((M, K)), dtype)
+    w, wh = to_dev(r.standard_normal((N, K)) / math.sqrt(K), dtype)
+    b = r.standard_normal(N).astype(np.float32)
+    ld = seq | 1
+    y = torch.empty((M, col0), device=DEV, dtype=tdtype(dtype))
+    vt = torch.full((M // seq, heads, dp, ld), 7.0, device=DEV, dtype=tdtype(dtype))
+    dn.op_linear_vt(dtype, x, dn.pack_weight(dtype, w, N, K), f32_dev(b), y, M, N, K, col0, vt, heads, dp, seq, ld)
+    torch.cuda.synchronize()
+    ref = L.linear(xh, wh, b.astype(np.float64))
+    assert rel_l2(host(y), ref[:, :col0]) < TOL[dtype]
+    got = host(vt)
+    assert rel_l2(got[..., :seq], ref[:, col0:].reshape(M // seq, seq, heads, dp).transpose(0, 2, 3, 1)) < TOL[dtype]
+    assert np.all(got[..., seq:] == 7)
 
 
 @pytest.mark.parametrize("dtype", DT)
