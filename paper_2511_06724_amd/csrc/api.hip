@@ -232,8 +232,8 @@ OpDev& op_dev_locked(int dev) {
 }
 
 template <typename T> dn::GemmPlan op_plan(const dn::GemmParams& p, int cus) {
-  return p.wscale ? dn::gemm_plan_fp8(p.M, p.N, p.K, p.geglu, cus, true, false, p.out_f32)
-                  : dn::gemm_plan<T>(p.M, p.N, p.K, p.geglu, cus, p.vt == nullptr, false, p.taps == 9, p.out_f32);
+  return p.wscale ? dn::gemm_plan_fp8(p.M, p.N, p.K, p.geglu, cus, false, p.out_f32)
+                  : dn::gemm_plan<T>(p.M, p.N, p.K, p.geglu, cus, p.vt != nullptr, false, p.taps == 9, p.out_f32);
 }
 
 template <typename T> void op_gemm(dn::GemmParams& p, hipStream_t s) {

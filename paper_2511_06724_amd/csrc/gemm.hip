@@ -419,6 +419,16 @@ static const TileCost kLinCost[] = {{128, 256, 0, 2, 5.2, 0.0, {0.684, 1.408}, 0
                                     {128, 160, 1, 2, 4.5, 0.0, {0.536, 1.083}, 0.094},
                                     {64, 160, 0, 1, 2.3, 0.0, {0.380}, 0.081},
                                     {128, 160, 0, 1, 3.1, 0.0, {0.636}, 0.097}};
+// Linear layers with a V^T output (attention input projections): unsplit, not on the four-wave
+// 128 x 160 tile, and with V^T's short stores, dearer in the wide tiles. 122 shapes of 128 to
+// 16384 rows: 0.3 % from the best plan in the mean, 6 % at most; priced as plain linear layers
+// 1.8 % and 19 %, or worse where the four-wave tile was chosen and the five-wave one ran
+// (12348 x 1536 x 320 54.5 us with V^T as it was then, 37.0 as it is, 27.2 on 64 x 128).
+static const TileCost kVtCost[] = {{128, 256, 0, 2, 6.24, 0.0, {0.703, 1.512}, 0.273},
+                                   {128, 128, 0, 2, 4.34, 0.0, {0.476, 0.904}, 0.239},
+                                   {64, 128, 0, 4, 3.73, 0.0, {0.285, 0.542, 0.869, 1.240}, 0.164},
+                                   {64, 160, 0, 1, 4.09, 0.0, {0.378}, 0.0},
+                                   {128, 160, 0, 1, 5.02, 0.0, {0.714}, 0.110}};
 static const TileCost kConvCost[] = {{128, 256, 0, 2, 5.7, 0.0, {0.803, 1.507}, 0.059},
                                      {128, 128, 0, 2, 4.0, 0.0, {0.567, 0.991}, 0.030},
                                      {64, 128, 0, 4, 3.5, 0.1, {0.359, 0.561, 0.866, 1.167}, 0.0},
@@ -427,10 +437,9 @@ static const TileCost kFp8Cost[] = {{128, 256, 0, 2, 2.7, 1.9, {1.037, 1.125}, 0
                                     {128, 128, 0, 2, 0.3, 0.0, {0.740, 0.838}, 0.225}};
 
 
-GemmPlan frag_plan(int M, int N, int K, int geglu, int cus, bool allow_split, bool fused_reduce, PlanKind kind,
-                   bool out_f32) {
-  const TileCost* vars = kind == kPlanConv ? kConvCost : kind == kPlanFp8 ? kFp8Cost : kLinCost;
-  const int nvars = kind == kPlanConv ? 4 : kind == kPlanFp8 ? 2 : 6;
+GemmPlan frag_plan(int M, int N, int K, int geglu, int cus, bool fused_reduce, PlanKind kind, bool out_f32) {
+  const TileCost* vars = kind == kPlanVt ? kVtCost : kind == kPlanConv ? kConvCost : kind == kPlanFp8 ? kFp8Cost : kLinCost;
+  const int nvars = kind == kPlanVt ? 5 : kind == kPlanConv ? 4 : kind == kPlanFp8 ? 2 : 6;
   const int nk = K / (kind == kPlanFp8 ? 128 : 64);
   const int min_stages = kind == kPlanFp8 ? 2 : 4;  // K stages a split part must have
   const double mn = (double)M * N / 1e6;
@@ -443,7 +452,7 @@ GemmPlan frag_plan(int M, int N, int K, int geglu, int cus, bool allow_split, bo
     const long long tiles = (long long)ceil_div(M, v.bm) * ceil_div(N, v.bn);
     const long long slots = (long long)cus * v.wg;
     for (int sp = 1; sp <= kMaxSplit; ++sp) {
-      if (sp > 1 && (geglu || !allow_split || nk / sp < min_stages)) break;
+      if (sp > 1 && (geglu || kind == kPlanVt || nk / sp < min_stages)) break;
       const long long units = tiles * sp, full = units / slots, rem = units % slots;
       const double st = (double)nk / sp;
       double t = full * (v.fixed + v.wgcost * v.wg + st * v.stage[v.wg - 1]);
@@ -487,10 +496,10 @@ GemmPlan frag_plan(int M, int N, int K, int geglu, int cus, bool allow_split, bo
 // needs 64-column value/gate pairs per wave, i.e. a block width of at least 128), else
 // 128 x 128 tiles with two resident workgroups per CU.
 template <typename T>
-GemmPlan gemm_plan(int M, int N, int K, int geglu, int cus, bool allow_split, bool fused_reduce, bool conv,
+GemmPlan gemm_plan(int M, int N, int K, int geglu, int cus, bool vt, bool fused_reduce, bool conv,
                    bool out_f32) {
   if (sizeof(T) == 2 && gemm_frag_layout(N, K))
-    return frag_plan(M, N, K, geglu, cus, allow_split, fused_reduce, conv ? kPlanConv : kPlanLinear, out_f32);
+    return frag_plan(M, N, K, geglu, cus, fused_reduce, conv ? kPlanConv : vt ? kPlanVt : kPlanLinear, out_f32);
   // fp32 with fewer 64 x 64 tiles than CUs: 32-column tiles whose waves split K
   if (sizeof(T) == 4 && (long long)ceil_div(M, 64) * ceil_div(N, 64) < cus) return GemmPlan{32, geglu ? 64 : 32};
   const long long t128 = (long long)ceil_div(M, 128) * ceil_div(N, 128);

@@ -403,6 +403,7 @@ __device__ __forceinline__ void wave_epilogue(const GemmParams& p, const f32x16 
     // residual: bf16 as whole 16-byte rows, one block t = i FN + j ahead (swapped into the
     // register layout when used), or fp32
     uint4 rb[2][2];
+    const bool pairs = p.vt && vt_pairs(p);
     const bool rb16 = p.resid && !p.resid_f32, rf32 = p.resid && p.resid_f32;
     auto load_resid = [&](int t) {
       if (!rb16) return;
@@ -442,7 +443,7 @@ __device__ __forceinline__ void wave_epilogue(const GemmParams& p, const f32x16 
           // rows are tokens; column nn of V^T is row nn of the sample's heads x dp
           bf16* dst = static_cast<bf16*>(p.vt) +
                       ((long long)vb * p.vt_heads * p.vt_dp + n - p.vt_col0 + h4) * p.vt_ld + vs;
-          if (vt_pairs(p)) {
+          if (__builtin_expect(pairs, true)) {
             // neighbouring lanes exchange one of two columns, so a lane stores two
             // consecutive tokens of a column (4 bytes; 64-byte segments)
             const bool odd = lane & 1;
@@ -1005,10 +1006,9 @@ template <int MODE> void dispatch_frag(const GemmParams& p, const GemmPlan& g, h
   if (g.bm == 64 && g.bn == 128) return run_frag<64, 1, 3, 2, 4, MODE>(p, g.split, s);
   if constexpr (MODE != 2) {
     if (g.bm == 64 && g.bn == 160) return run_frag<64, 1, 3, 3, 2, MODE, 5>(p, g.split, s);
-    // X5 takes no V^T output
-    if (g.bm == 128 && g.bn == 160 && (!g.x5 || p.vt)) return run_frag<128, 1, 3, 3, 2, MODE, 5>(p, g.split, s);
+    if (g.bm == 128 && g.bn == 160 && !g.x5) return run_frag<128, 1, 3, 3, 2, MODE, 5>(p, g.split, s);
   }
-  if (g.bm == 128 && g.bn == 160) return run_frag<128, 1, 3, 2, 2, MODE, 4, true>(p, g.split, s);
+  if (g.bm == 128 && g.bn == 160 && g.x5) return run_frag<128, 1, 3, 2, 2, MODE, 4, true>(p, g.split, s);
   throw Error(-1, "gemm: no fragment-B kernel for this tile plan");
 }
 
@@ -1279,8 +1279,8 @@ bool gemm_fp8_layout(int N, int K) { return N >= 32 && N % 32 == 0 && K >= 128 &
 
 size_t gemm_fp8_code_bytes(int N, int K) { return (size_t)((N + 31) / 32 * 32) * K; }
 
-GemmPlan gemm_plan_fp8(int M, int N, int K, int geglu, int cus, bool allow_split, bool fused_reduce, bool out_f32) {
-  return frag_plan(M, N, K, geglu, cus, allow_split, fused_reduce, kPlanFp8, out_f32);
+GemmPlan gemm_plan_fp8(int M, int N, int K, int geglu, int cus, bool fused_reduce, bool out_f32) {
+  return frag_plan(M, N, K, geglu, cus, fused_reduce, kPlanFp8, out_f32);
 }
 
 void gemm_fp8(const GemmParams& p, const GemmPlan& g, hipStream_t s) {
@@ -1312,6 +1312,7 @@ void gemm_bf16_frag(const GemmParams& p, const GemmPlan& g, hipStream_t s) {
   DN_CHECK(p.taps == 1 || p.c1 == 0, "gemm: the fragment-B conv takes one input source");
   DN_CHECK(g.split >= 1 && g.split <= kMaxSplit && p.K / kBK >= g.split, "gemm: bad split");
   DN_CHECK(!p.geglu || (g.bn / 4) % 64 == 0, "gemm: GEGLU needs 64-column value/gate pairs per wave");
+  DN_CHECK(!(p.vt && g.x5), "gemm: the four-wave 128 x 160 tile takes no V^T output");
   if (g.split > 1 || p.raw_partial) {
     DN_CHECK(!p.geglu && !p.vt, "gemm: split-K takes neither GEGLU nor the V^T output");
     DN_CHECK(p.n_store % 4 == 0 && p.n_store == p.N, "gemm: split-K needs n_store == N, a multiple of 4");

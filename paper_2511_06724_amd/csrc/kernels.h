@@ -64,17 +64,16 @@ struct GemmPlan {
   int tail_bands = 0;    // fragment-B 128 x 256 tiles: the last column bands as 64-row tiles
 };
 constexpr int kMaxSplit = 8;
-// allow_split = false for epilogues split-K does not support (the per-head V^T output);
+// vt: with the per-head V^T output (unsplit, and not on the four-wave 128 x 160 tile);
 // fused_reduce: the partial slabs are summed by the consumer (layernorm_reduce), so a
 // split costs only the extra slab reads.
 template <typename T>
-GemmPlan gemm_plan(int M, int N, int K, int geglu, int cus, bool allow_split = true, bool fused_reduce = false,
+GemmPlan gemm_plan(int M, int N, int K, int geglu, int cus, bool vt = false, bool fused_reduce = false,
                    bool conv = false, bool out_f32 = false);
 template <typename T> void gemm(const GemmParams& p, const GemmPlan& g, hipStream_t s);
 // The fragment-B kernels' tile plan (a cost model fitted to measured launches).
-enum PlanKind { kPlanLinear, kPlanConv, kPlanFp8 };
-GemmPlan frag_plan(int M, int N, int K, int geglu, int cus, bool allow_split, bool fused_reduce, PlanKind kind,
-                   bool out_f32);
+enum PlanKind { kPlanLinear, kPlanVt, kPlanConv, kPlanFp8 };
+GemmPlan frag_plan(int M, int N, int K, int geglu, int cus, bool fused_reduce, PlanKind kind, bool out_f32);
 void gemm_bf16_frag(const GemmParams& p, const GemmPlan& g, hipStream_t s);
 // bf16 weight matrices [N][K] with gemm_frag_layout(N, K) are stored in MFMA fragment
 // order (gemm_frag.hip) and multiplied by the fragment-B kernel; every other shape,
@@ -83,8 +82,7 @@ bool gemm_frag_layout(int N, int K);
 // fp8 (E4M3) GEMM: A fp8 codes [M][lda], B a matrix packed by pack_fp8 (codes in the
 // fragment order of the 32x32x64 fp8 matrix-core step, fp32 row scales in p.wscale);
 // N % 32 == 0, K % 128 == 0. Tile plans 128 x 256 and 128 x 128, split-K as gemm_plan.
-GemmPlan gemm_plan_fp8(int M, int N, int K, int geglu, int cus, bool allow_split, bool fused_reduce,
-                       bool out_f32 = false);
+GemmPlan gemm_plan_fp8(int M, int N, int K, int geglu, int cus, bool fused_reduce, bool out_f32 = false);
 void gemm_fp8(const GemmParams& p, const GemmPlan& g, hipStream_t s);
 bool gemm_fp8_layout(int N, int K);
 size_t gemm_fp8_code_bytes(int N, int K);  // N rounded up to 32, times K

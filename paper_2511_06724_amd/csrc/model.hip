@@ -812,8 +812,8 @@ template <typename T> struct Exec {
   size_t split_need = 0;  // dry walk: largest split-K workspace (floats) of the step
 
   void run_gemm(GemmParams& p) {
-    const GemmPlan g = p.wscale ? gemm_plan_fp8(p.M, p.N, p.K, p.geglu, m->cus, true, false, p.out_f32)
-                                : gemm_plan<T>(p.M, p.N, p.K, p.geglu, m->cus, p.vt == nullptr, false, p.taps == 9,
+    const GemmPlan g = p.wscale ? gemm_plan_fp8(p.M, p.N, p.K, p.geglu, m->cus, false, p.out_f32)
+                                : gemm_plan<T>(p.M, p.N, p.K, p.geglu, m->cus, p.vt != nullptr, false, p.taps == 9,
                                                p.out_f32);
     if (dry) {
       split_need = std::max(split_need, gemm_workspace_floats(g, p.M, p.N));
@@ -968,8 +968,8 @@ template <typename T> struct Exec {
     bool resid = true;
   };
   Pending residual_gemm(const LinW& w, const void* x, int ldx, long long M, bool resid) {
-    const GemmPlan g = w.scale ? gemm_plan_fp8(static_cast<int>(M), w.n, w.k, 0, m->cus, true, true, true)
-                               : gemm_plan<T>(static_cast<int>(M), w.n, w.k, 0, m->cus, true, true, false, true);
+    const GemmPlan g = w.scale ? gemm_plan_fp8(static_cast<int>(M), w.n, w.k, 0, m->cus, true, true)
+                               : gemm_plan<T>(static_cast<int>(M), w.n, w.k, 0, m->cus, false, true, false, true);
     if (!g.frag || g.split == 1) {
       linear(w, x, ldx, M, m->R, w.n, true, resid ? m->R : nullptr, w.n, true);
       return Pending{};

@@ -380,7 +380,7 @@ template <typename T> struct VaeExec {
   void need_act(long long e) { act = std::max(act, (size_t)e); }
 
   void gemm_(GemmParams& p) {
-    const GemmPlan g = gemm_plan<T>(p.M, p.N, p.K, 0, v->cus, p.vt == nullptr, false, p.taps == 9, p.out_f32);
+    const GemmPlan g = gemm_plan<T>(p.M, p.N, p.K, 0, v->cus, p.vt != nullptr, false, p.taps == 9, p.out_f32);
     if (dry) {
       split = std::max(split, gemm_workspace_floats(g, p.M, p.N));
       return;

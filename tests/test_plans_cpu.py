@@ -1,0 +1,16 @@
+"""The fragment-B GEMM's tile plans (dn::frag_plan, a host function of the library): plans only
+name kernels that run, and the shapes of the GPU operator tests reach every kernel."""
+
+from tests.plans import LINEAR, VT, plan
+
+
+def test_vt_output_never_plans_a_kernel_that_does_not_run():
+    """Projections with a V^T output run unsplit and not on the four-wave 128 x 160 tile:
+    the plan may not price that tile for them, at any size of the sublayers."""
+    for heads, K in ((20, 1280), (10, 640), (8, 320), (5, 320), (20, 2048), (10, 768), (8, 768)):
+        for n in (1, 2, 4, 8):
+            for tokens in [77, *range(64, 1100, 31), *range(1100, 4200, 293)]:
+                g = plan(n * tokens, 3 * 64 * heads, K, VT)
+                assert (g.x5, g.split, g.frag) == (0, 1, 1), (n * tokens, heads, K)
+    # the same sizes without V^T do use it
+    assert any(plan(2 * t, 960, 320, LINEAR).x5 for t in range(64, 4200, 31))
