@@ -238,7 +238,8 @@ __device__ __forceinline__ void generic_rows(const GemmParams& p, const float* e
 // The wave's blocks acc[i][j] (rows m0 + 32 i .., columns nw0 + 32 j ..), i < FM, j < FN.
 // pin: with use_pin, the fp32 residual of the kEpiF32 kind already in registers.
 // ep: 32 x (32 FN + 4) floats of LDS of this wave (generic path).
-template <int FM, int FN, bool SPLIT, bool SCALE, bool PIN>
+// VT: the launch may have a V^T output (else its code stays out of the kernel).
+template <int FM, int FN, bool SPLIT, bool SCALE, bool PIN, bool VT>
 __device__ __forceinline__ void wave_epilogue(const GemmParams& p, const f32x16 (*acc)[FN], const int m0, const int nw0,
                                               const int split, const int kind, const f32x4 (*pin)[FN][4], const bool use_pin,
                                               float* ep) {
@@ -403,7 +404,7 @@ __device__ __forceinline__ void wave_epilogue(const GemmParams& p, const f32x16 
     // residual: bf16 as whole 16-byte rows, one block t = i FN + j ahead (swapped into the
     // register layout when used), or fp32
     uint4 rb[2][2];
-    const bool pairs = p.vt && vt_pairs(p);
+    const bool pairs = VT && p.vt && vt_pairs(p);
     const bool rb16 = p.resid && !p.resid_f32, rf32 = p.resid && p.resid_f32;
     auto load_resid = [&](int t) {
       if (!rb16) return;
@@ -427,7 +428,7 @@ __device__ __forceinline__ void wave_epilogue(const GemmParams& p, const f32x16 
           rf32 ? static_cast<const float*>(p.resid) + (long long)min(m, p.M - 1) * p.ldr + h4 : nullptr;
       // V^T output: sample and token of the row
       int vb = 0, vs = 0;
-      if (p.vt && nw0 + 32 * FN > p.vt_col0) {
+      if (VT && p.vt && nw0 + 32 * FN > p.vt_col0) {
         vb = m / p.vt_seq;
         vs = m - vb * p.vt_seq;
       }
@@ -439,7 +440,7 @@ __device__ __forceinline__ void wave_epilogue(const GemmParams& p, const f32x16 
         float v[4][4];
 #pragma unroll
         for (int g = 0; g < 4; ++g) biased(acc[i][j], n, g, bias[j][g], v[g]);
-        if (p.vt && n + 32 > p.vt_col0) {
+        if (VT && p.vt && n + 32 > p.vt_col0) {
           // rows are tokens; column nn of V^T is row nn of the sample's heads x dp
           bf16* dst = static_cast<bf16*>(p.vt) +
                       ((long long)vb * p.vt_heads * p.vt_dp + n - p.vt_col0 + h4) * p.vt_ld + vs;
@@ -849,13 +850,13 @@ __device__ __forceinline__ void frag_tile(const GemmParams& p, const int m0, con
         for (int r = 0; r < 16; ++r) blk5[0][0][r] += part5[((w * FM + wave) * 16 + r) * 64 + lane];
     }
     __syncthreads();
-    wave_epilogue<FM, FN, SPLIT, false, false>(p, acc, m0, nw0, split, kind, nullptr, false, ep);
+    wave_epilogue<FM, FN, SPLIT, false, false, false>(p, acc, m0, nw0, split, kind, nullptr, false, ep);
     if (wave < FM && n0 + 128 < p.N)
-      wave_epilogue<1, 1, SPLIT, false, false>(p, blk5, m0 + wave * 32, n0 + 128, split, kind, nullptr, false, ep);
+      wave_epilogue<1, 1, SPLIT, false, false, false>(p, blk5, m0 + wave * 32, n0 + 128, split, kind, nullptr, false, ep);
   } else if constexpr (kPreIn) {
-    wave_epilogue<FM, FN, SPLIT, false, true>(p, acc, m0, nw0, split, kind, pin, pre_in, ep);
+    wave_epilogue<FM, FN, SPLIT, false, true, MODE == 0>(p, acc, m0, nw0, split, kind, pin, pre_in, ep);
   } else {
-    wave_epilogue<FM, FN, SPLIT, false, false>(p, acc, m0, nw0, split, kind, nullptr, false, ep);
+    wave_epilogue<FM, FN, SPLIT, false, false, MODE == 0>(p, acc, m0, nw0, split, kind, nullptr, false, ep);
   }
 }
 
@@ -1163,7 +1164,7 @@ __device__ __forceinline__ void fp8_tile(const GemmParams& p, const int m0, cons
   __syncthreads();
 
   float* ep = reinterpret_cast<float*>(smem) + wave * (32 * (WN + 4));
-  wave_epilogue<FM, FN, SPLIT, true, false>(p, acc, m0, n0 + wave * WN, split, SPLIT ? 0 : epi_kind(p), nullptr, false, ep);
+  wave_epilogue<FM, FN, SPLIT, true, false, false>(p, acc, m0, n0 + wave * WN, split, SPLIT ? 0 : epi_kind(p), nullptr, false, ep);
 }
 
 // The fp8 kernel: unit assignment as gemm_frag_kernel (XCD-contiguous; with TBM > 0 and
@@ -1312,7 +1313,8 @@ void gemm_bf16_frag(const GemmParams& p, const GemmPlan& g, hipStream_t s) {
   DN_CHECK(p.taps == 1 || p.c1 == 0, "gemm: the fragment-B conv takes one input source");
   DN_CHECK(g.split >= 1 && g.split <= kMaxSplit && p.K / kBK >= g.split, "gemm: bad split");
   DN_CHECK(!p.geglu || (g.bn / 4) % 64 == 0, "gemm: GEGLU needs 64-column value/gate pairs per wave");
-  DN_CHECK(!(p.vt && g.x5), "gemm: the four-wave 128 x 160 tile takes no V^T output");
+  DN_CHECK(!p.vt || (p.taps == 1 && p.c1 == 0 && !g.x5),
+           "gemm: the V^T output takes a plain linear layer, and not the four-wave 128 x 160 tile");
   if (g.split > 1 || p.raw_partial) {
     DN_CHECK(!p.geglu && !p.vt, "gemm: split-K takes neither GEGLU nor the V^T output");
     DN_CHECK(p.n_store % 4 == 0 && p.n_store == p.N, "gemm: split-K needs n_store == N, a multiple of 4");
