@@ -396,19 +396,17 @@ template <typename T, bool CONV> void dispatch(const GemmParams& p, const GemmPl
 }  // namespace
 
 // Fragment-B kernels: tile, split and tail bands by a cost model fitted to launches measured
-// on MI355X (bf16: 147 shapes x every tile and split, linear layers and implicit convolutions
-// apart; fp8: 29 shapes). A tile variant runs up to `wg` workgroups per CU; with c of them on
-// the busiest CU a K stage (64 bf16 or 128 fp8 values) takes stage[c - 1] us, so a round of
-// units costs fixed + wgcost c + stages x stage[c - 1], a grid is its full rounds plus the
+// on MI355X (every tile and split of 804 shapes; weights from HBM, activations as the launch
+// before leaves them). A tile variant runs up to `wg` workgroups per CU; with c of them on the
+// busiest CU a K stage (64 bf16 or 128 fp8 values) takes stage[c - 1] us, so a round of units
+// costs fixed + wgcost c + stages x stage[c - 1], a grid is its full rounds plus the
 // remainder's round, and the outputs cost per_mb us per MB written (an fp32 output also reads
-// its residual). The stage times are what the old model missed: a lone 128 x 256 workgroup
-// needs 0.68 us per stage where two together need 1.41, so a half-filled round is not half
-// the price. Splitting K adds the reduction launch and its slab traffic, or, when a LayerNorm
-// sums the slabs, that kernel's extra reads. Over the measured shapes the chosen plan is 0.6 %
-// from the best one (geometric mean; 9 % for linear layers and 12 % for convolutions before:
-// decoder convolutions of 256 and 512 channels were 128 x 160 tiles with 20 % padding, 785 ->
-// 562 us at 262144 x 256 x 4608, and short linear layers were split, 16.8 -> 9.7 us at
-// 1152 x 1280 x 1280).
+// its residual). In bf16 a stage's time nearly doubles with a second workgroup on the CU (a
+// 128 x 256 linear tile 0.68 -> 1.41 us), so that filling a round's second half costs about as
+// much as its first; in fp8 it hardly grows (0.78 -> 1.06). Splitting K adds the reduction
+// launch (reduce us) and its slab traffic (at reduce_mb MB / us), or, when a LayerNorm sums the
+// slabs, that kernel's extra reads. The chosen plan against the best one: 0.4 to 0.5 % in the
+// mean for linear layers (332 shapes), V^T (122), convolutions (215) and fp8 (135).
 struct TileCost {
   int bm, bn, x5, wg;
   double fixed, wgcost, stage[4], per_mb;
@@ -421,33 +419,46 @@ static const TileCost kLinCost[] = {{128, 256, 0, 2, 5.2, 0.0, {0.684, 1.408}, 0
                                     {128, 160, 0, 1, 3.1, 0.0, {0.636}, 0.097}};
 // Linear layers with a V^T output (attention input projections): unsplit, not on the four-wave
 // 128 x 160 tile, and with V^T's short stores, dearer in the wide tiles. 122 shapes of 128 to
-// 16384 rows: 0.3 % from the best plan in the mean, 6 % at most; priced as plain linear layers
-// 1.8 % and 19 %, or worse where the four-wave tile was chosen and the five-wave one ran
+// 16384 rows: 0.4 % from the best plan in the mean; priced as plain linear layers 1.8 %, and
+// more where the four-wave tile was chosen and the five-wave one ran
 // (12348 x 1536 x 320 54.5 us with V^T as it was then, 37.0 as it is, 27.2 on 64 x 128).
 static const TileCost kVtCost[] = {{128, 256, 0, 2, 6.24, 0.0, {0.703, 1.512}, 0.273},
                                    {128, 128, 0, 2, 4.34, 0.0, {0.476, 0.904}, 0.239},
                                    {64, 128, 0, 4, 3.73, 0.0, {0.285, 0.542, 0.869, 1.240}, 0.164},
                                    {64, 160, 0, 1, 4.09, 0.0, {0.378}, 0.0},
                                    {128, 160, 0, 1, 5.02, 0.0, {0.714}, 0.110}};
-static const TileCost kConvCost[] = {{128, 256, 0, 2, 5.7, 0.0, {0.803, 1.507}, 0.059},
-                                     {128, 128, 0, 2, 4.0, 0.0, {0.567, 0.991}, 0.030},
-                                     {64, 128, 0, 4, 3.5, 0.1, {0.359, 0.561, 0.866, 1.167}, 0.0},
-                                     {128, 160, 1, 2, 5.1, 0.0, {0.644, 1.124}, 0.066}};
+// Convolutions, upsampling and strided ones among them. A 128 x 256 workgroup alone on a CU takes
+// 0.94 us a stage and two together 1.55, so the 2048-row convolutions run in six parts, two
+// workgroups per CU, not three parts with one: 512 pixels x 1280 x 11520 upsampled 98.8 ->
+// 82.9 us, 2048 x 1280 x 23040 142 -> 133.
+static const TileCost kConvCost[] = {{128, 256, 0, 2, 1.957, 0.0, {0.941, 1.549}, 0.296},
+                                     {128, 128, 0, 2, 2.370, 0.0, {0.647, 1.019}, 0.278},
+                                     {64, 128, 0, 4, 1.522, 0.034, {0.402, 0.600, 0.962, 1.171}, 0.278},
+                                     {128, 160, 1, 2, 3.905, 0.0, {0.662, 1.110}, 0.315}};
 static const TileCost kFp8Cost[] = {{128, 256, 0, 2, 2.7, 1.9, {1.037, 1.125}, 0.067},
                                     {128, 128, 0, 2, 0.3, 0.0, {0.740, 0.838}, 0.225}};
 
+// by PlanKind; reduce in us, reduce_mb in us per MB (slabs read, outputs written)
+struct PlanCost {
+  const TileCost* tiles;
+  int n;
+  double reduce, reduce_mb;
+};
+static const PlanCost kPlanCost[] = {{kLinCost, 6, 3.5, 1 / 6.0},
+                                     {kVtCost, 5, 0.0, 0.0},  // never split
+                                     {kConvCost, 4, 5.745, 0.011},
+                                     {kFp8Cost, 2, 3.5, 1 / 6.0}};
 
 GemmPlan frag_plan(int M, int N, int K, int geglu, int cus, bool fused_reduce, PlanKind kind, bool out_f32) {
-  const TileCost* vars = kind == kPlanVt ? kVtCost : kind == kPlanConv ? kConvCost : kind == kPlanFp8 ? kFp8Cost : kLinCost;
-  const int nvars = kind == kPlanVt ? 5 : kind == kPlanConv ? 4 : kind == kPlanFp8 ? 2 : 6;
+  const PlanCost& cost = kPlanCost[kind];
   const int nk = K / (kind == kPlanFp8 ? 128 : 64);
   const int min_stages = kind == kPlanFp8 ? 2 : 4;  // K stages a split part must have
   const double mn = (double)M * N / 1e6;
   GemmPlan best{128, 256};
   best.frag = 1;
   double best_t = 1e300;
-  for (int vi = 0; vi < nvars; ++vi) {
-    const TileCost& v = vars[vi];
+  for (int vi = 0; vi < cost.n; ++vi) {
+    const TileCost& v = cost.tiles[vi];
     if (geglu && v.bn != 256) continue;  // GEGLU needs 64-column value / gate pairs per wave
     const long long tiles = (long long)ceil_div(M, v.bm) * ceil_div(N, v.bn);
     const long long slots = (long long)cus * v.wg;
@@ -464,7 +475,7 @@ GemmPlan frag_plan(int M, int N, int K, int geglu, int cus, bool fused_reduce, P
         t += v.per_mb * mn * (geglu ? 1 : out_f32 ? 8 : 2);
       } else {
         t += v.per_mb * mn * 4 * sp;
-        t += fused_reduce ? 1.5 + mn * 4 * (sp + 1) / 7.0 : 3.5 + mn * (4 * sp + (out_f32 ? 8 : 2)) / 6.0;
+        t += fused_reduce ? 1.5 + mn * 4 * (sp + 1) / 7.0 : cost.reduce + mn * (4 * sp + (out_f32 ? 8 : 2)) * cost.reduce_mb;
       }
       if (t < best_t) {
         best_t = t;

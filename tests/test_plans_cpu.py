@@ -1,7 +1,9 @@
 """The fragment-B GEMM's tile plans (dn::frag_plan, a host function of the library): plans only
 name kernels that run, and the shapes of the GPU operator tests reach every kernel."""
 
-from tests.plans import LINEAR, VT, plan
+import pytest
+
+from tests.plans import CONV, LINEAR, VT, plan
 
 
 def test_vt_output_never_plans_a_kernel_that_does_not_run():
@@ -14,3 +16,16 @@ def test_vt_output_never_plans_a_kernel_that_does_not_run():
                 assert (g.x5, g.split, g.frag) == (0, 1, 1), (n * tokens, heads, K)
     # the same sizes without V^T do use it
     assert any(plan(2 * t, 960, 320, LINEAR).x5 for t in range(64, 4200, 31))
+
+
+@pytest.mark.parametrize("M,N,K,want,us,other", [
+    (2048, 1280, 11520, (128, 256, 0, 6), 82.9, "three parts 98.8 (upsampled input)"),
+    (2048, 1280, 17280, (128, 256, 0, 6), 104.2, "three parts 108.6"),
+    (2048, 1280, 23040, (128, 256, 0, 6), 133.2, "three parts 142.3"),
+    (8192, 640, 8640, (128, 160, 1, 1), 105.1, "two parts 112.3"),
+])
+def test_convolution_plans_are_the_measured_best(M, N, K, want, us, other):
+    """SD-XL convolutions whose plans lie close together in the cost model and far apart on the
+    device (us measured for the wanted plan and for its nearest rival)."""
+    g = plan(M, N, K, CONV)
+    assert (g.bm, g.bn, g.x5, g.split) == want, f"{us} us wanted, {other}"
