@@ -428,9 +428,9 @@ static const TileCost kVtCost[] = {{128, 256, 0, 2, 6.24, 0.0, {0.703, 1.512}, 0
                                    {64, 160, 0, 1, 4.09, 0.0, {0.378}, 0.0},
                                    {128, 160, 0, 1, 5.02, 0.0, {0.714}, 0.110}};
 // Convolutions, upsampling and strided ones among them. A 128 x 256 workgroup alone on a CU takes
-// 0.94 us a stage and two together 1.55, so the 2048-row convolutions run in six parts, two
-// workgroups per CU, not three parts with one: 512 pixels x 1280 x 11520 upsampled 98.8 ->
-// 82.9 us, 2048 x 1280 x 23040 142 -> 133.
+// 0.94 us a stage and two together 1.55, so the 2048-row convolutions run as two workgroups per
+// CU (six parts, or four of 128 x 160), not as three parts with one: 512 pixels x 1280 x 11520
+// upsampled 98.8 -> 82.9 us, 2048 x 1280 x 23040 142 -> 133.
 static const TileCost kConvCost[] = {{128, 256, 0, 2, 1.957, 0.0, {0.941, 1.549}, 0.296},
                                      {128, 128, 0, 2, 2.370, 0.0, {0.647, 1.019}, 0.278},
                                      {64, 128, 0, 4, 1.522, 0.034, {0.402, 0.600, 0.962, 1.171}, 0.278},

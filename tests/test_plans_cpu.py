@@ -19,7 +19,7 @@ def test_vt_output_never_plans_a_kernel_that_does_not_run():
 
 
 @pytest.mark.parametrize("M,N,K,want,us,other", [
-    (2048, 1280, 11520, (128, 256, 0, 6), 82.9, "three parts 98.8 (upsampled input)"),
+    (2048, 1280, 11520, (128, 160, 1, 4), 82.9, "128 x 256 in three parts 98.8 (upsampled input)"),
     (2048, 1280, 17280, (128, 256, 0, 6), 104.2, "three parts 108.6"),
     (2048, 1280, 23040, (128, 256, 0, 6), 133.2, "three parts 142.3"),
     (8192, 640, 8640, (128, 160, 1, 1), 105.1, "two parts 112.3"),
