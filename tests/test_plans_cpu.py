@@ -3,7 +3,7 @@ name kernels that run, and the shapes of the GPU operator tests reach every kern
 
 import pytest
 
-from tests.plans import CONV, LINEAR, VT, plan
+from tests.plans import CONV, FP8, LINEAR, VT, plan
 
 
 def test_vt_output_never_plans_a_kernel_that_does_not_run():
@@ -29,3 +29,13 @@ def test_convolution_plans_are_the_measured_best(M, N, K, want, us, other):
     device (us measured for the wanted plan and for its nearest rival)."""
     g = plan(M, N, K, CONV)
     assert (g.bm, g.bn, g.x5, g.split) == want, f"{us} us wanted, {other}"
+
+
+@pytest.mark.parametrize("M,N,K,want,us,other", [
+    (16384, 320, 1280, (128, 128, 1), 24.0, "128 x 256 26.7"),
+    (1152, 320, 1280, (128, 128, 3), 10.9, "unsplit 13.6"),
+])
+def test_fp8_plans_are_the_measured_best(M, N, K, want, us, other):
+    """Feed-forward outputs of 320 channels with an fp32 residual (as above)."""
+    g = plan(M, N, K, FP8, out_f32=True)
+    assert (g.bm, g.bn, g.split) == want, f"{us} us wanted, {other}"
