@@ -503,6 +503,25 @@ GemmPlan frag_plan(int M, int N, int K, int geglu, int cus, bool fused_reduce, P
   return best;
 }
 
+// Which fp32 launches take the 32-column tiles whose waves split K. Their operands come straight
+// from global memory, so the form pays while a CU gets one workgroup; with more, the other
+// workgroups' re-reads cost what the shorter walk gains. Measured (us, 64 x 64 or, with GEGLU,
+// 128 x 128 tiles -> these), units being 32-row tiles:
+//  - linear, up to one per CU: 512 x 256 x 576 18.4 -> 10.3, 512 x 512 x 5120 124.8 -> 51.1; at
+//    K = 64, one step per wave, 5.7 -> 6.2, so from 96 on. Two per CU only for long K and where
+//    an operand value meets enough others: 1024 x 512 x 2560 65.3 -> 50.0, but x 64 6.6 -> 11.2,
+//    8192 x 64 x 1280 36.6 -> 39.6. Four per CU: 1024 x 960 x 1280 36.1 -> 57.0.
+//  - GEGLU, up to one: 512 x 2 x 512 x 64 11.5 -> 8.2; two: x 128 16.0 -> 15.2, x 64 11.6 -> 14.7.
+//  - convolutions (whose 64-row tiles wait on their gathers), up to two: 8192 x 64 x 576 21.6 ->
+//    17.4; three: 4096 x 192 x 1152 38.2 -> 34.0, x 288 12.9 -> 15.3; 2048 x 448 x 2880 87.8 -> 102.
+bool wavesplit(int M, int N, int K, int geglu, bool conv, int cus) {
+  const long long units = (long long)ceil_div(M, 32) * ceil_div(N, geglu ? 64 : 32);
+  if (conv) return units <= 2ll * cus || (units <= 3ll * cus && K >= 1152);
+  if (geglu) return units <= cus || (units <= 2ll * cus && K >= 256);
+  if (units <= cus) return K > 64;
+  return units <= 2ll * cus && K >= 1024 && (long long)M * N >= 120ll * ((long long)M + N);
+}
+
 // Tile choice of the register-staged kernel (fp32, the check mode, and bf16 shapes the
 // fragment layout does not take: N % 32 != 0 or K % 64 != 0, e.g. conv_in and the
 // output head): 64 x 64 tiles when there are fewer 128 x 128 tiles than CUs (GEGLU
@@ -513,8 +532,7 @@ GemmPlan gemm_plan(int M, int N, int K, int geglu, int cus, bool vt, bool fused_
                    bool out_f32) {
   if (sizeof(T) == 2 && gemm_frag_layout(N, K))
     return frag_plan(M, N, K, geglu, cus, fused_reduce, conv ? kPlanConv : vt ? kPlanVt : kPlanLinear, out_f32);
-  // fp32 with fewer 64 x 64 tiles than CUs: 32-column tiles whose waves split K
-  if (sizeof(T) == 4 && (long long)ceil_div(M, 64) * ceil_div(N, 64) < cus) return GemmPlan{32, geglu ? 64 : 32};
+  if (sizeof(T) == 4 && wavesplit(M, N, K, geglu, conv, cus)) return GemmPlan{32, geglu ? 64 : 32};
   const long long t128 = (long long)ceil_div(M, 128) * ceil_div(N, 128);
   if (!geglu && t128 < cus) return GemmPlan{64, 64};
   return GemmPlan{128, 128};

@@ -19,3 +19,12 @@ _frag_plan.restype = Plan
 
 def plan(M, N, K, kind=LINEAR, geglu=False, fused_reduce=False, out_f32=False):
     return _frag_plan(M, N, K, int(geglu), CUS, fused_reduce, kind, out_f32)
+
+
+_plan32 = getattr(dn.lib, "_ZN2dn9gemm_planIfEENS_8GemmPlanEiiiiibbbb")
+_plan32.argtypes = [C.c_int] * 5 + [C.c_bool] * 4
+_plan32.restype = Plan
+
+
+def plan_fp32(M, N, K, geglu=False, conv=False):
+    return _plan32(M, N, K, int(geglu), CUS, False, False, conv, False)

@@ -104,10 +104,12 @@ def test_linear_epilogue_forms(M, N, K, off):
             assert (buf[off + M * N:].float() == 7).all() and (buf[:off].float() == 7).all()
 
 
-@pytest.mark.parametrize("M,N,K", [(1, 4, 32), (33, 30, 32), (31, 100, 96), (70, 33, 64), (512, 64, 576), (1000, 65, 160)])
+@pytest.mark.parametrize("M,N,K", [(1, 4, 32), (33, 30, 32), (31, 100, 96), (70, 33, 64), (512, 64, 576), (1000, 65, 160),
+                                   (1, 3, 96), (65, 31, 128), (1025, 225, 96), (1020, 500, 1056)])
 def test_linear_fp32_small(M, N, K):
-    """fp32 grids below the CU count (32-column tiles whose eight waves split K): fewer K
-    steps than waves, uneven shares, ragged rows and columns, with a residual. Exact products,
+    """Small fp32 grids: from K = 96 on 32-column tiles whose eight waves split K (shares of one
+    and two steps, uneven shares, ragged rows and columns, one and two workgroups per CU, and
+    the first size past them: 1025 x 225), 64 x 64 tiles below; with a residual. Exact products,
     fp32 sums: TOL."""
     announce(f"linear fp32 small M={M} N={N} K={K}")
     r = _rng(M + N + K)
@@ -149,6 +151,13 @@ def test_linear_geglu(dtype, M, N, K):
     u = L.linear(xh, w1h, b1.astype(np.float64))
     ref = u[:, :N] * L.gelu(u[:, N:])
     assert rel_l2(host(y), ref) < TOL[dtype]
+
+
+@pytest.mark.parametrize("M,N,K", [(33, 32, 32), (70, 96, 96), (500, 1280, 320), (500, 1280, 32)])
+def test_linear_geglu_fp32_small(M, N, K):
+    """fp32 GEGLU whose eight waves split K: fewer K steps than waves, one and two workgroups
+    per CU; the last shape has two and too short a K, and runs 128 x 128 tiles."""
+    test_linear_geglu(dn.DN_FP32, M, N, K)
 
 
 @pytest.mark.parametrize("dtype", DT)

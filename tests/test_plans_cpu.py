@@ -3,7 +3,7 @@ name kernels that run, and the shapes of the GPU operator tests reach every kern
 
 import pytest
 
-from tests.plans import CONV, FP8, LINEAR, VT, plan
+from tests.plans import CONV, FP8, LINEAR, VT, plan, plan_fp32
 
 
 def test_vt_output_never_plans_a_kernel_that_does_not_run():
@@ -39,3 +39,19 @@ def test_fp8_plans_are_the_measured_best(M, N, K, want, us, other):
     """Feed-forward outputs of 320 channels with an fp32 residual (as above)."""
     g = plan(M, N, K, FP8, out_f32=True)
     assert (g.bm, g.bn, g.split) == want, f"{us} us wanted, {other}"
+
+
+@pytest.mark.parametrize("M,N,K,kind,waves,us,other", [
+    (512, 512, 576, "linear", True, 10.8, 18.6), (512, 512, 64, "linear", False, 5.7, 6.2),
+    (1024, 512, 2560, "linear", True, 50.0, 65.3), (1024, 512, 64, "linear", False, 6.6, 11.2),
+    (8192, 64, 1280, "linear", False, 36.6, 39.6), (1024, 960, 1280, "linear", False, 36.1, 57.0),
+    (16256, 64, 5120, "linear", False, 133.3, 299.6), (64, 16320, 576, "linear", False, 20.8, 41.9),
+    (512, 1024, 64, "geglu", True, 8.2, 11.5), (512, 1280, 64, "geglu", False, 11.6, 14.7),
+    (512, 1280, 320, "geglu", True, 18.7, 29.0), (8192, 64, 576, "conv", True, 17.4, 21.6),
+    (4096, 192, 1152, "conv", True, 34.0, 38.2), (4096, 192, 288, "conv", False, 12.9, 15.3),
+    (2048, 448, 2880, "conv", False, 87.8, 102.2)])
+def test_fp32_launches_split_k_over_waves_only_where_faster(M, N, K, kind, waves, us, other):
+    """Both forms measured (us of the wanted one, then of the other) on each side of every line
+    of the rule."""
+    g = plan_fp32(M, N, K, geglu=kind == "geglu", conv=kind == "conv")
+    assert (g.bm == 32) == waves, f"{us} us wanted, {other}"
