@@ -572,10 +572,13 @@ dn_status dn_op_attention(int32_t dtype, const void* q, int32_t ldq, const void*
     a.Sq = Sq;
     a.Skv = Skv;
     a.scale_log2 = scale * 1.4426950408889634f;
+    int dev = 0, cus = 0;
+    DN_HIP(hipGetDevice(&dev));
+    DN_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     if (dtype == DN_BF16)
-      dn::attention<dn::bf16>(a, head_stride, as_stream(stream));
+      dn::attention<dn::bf16>(a, head_stride, cus, as_stream(stream));
     else
-      dn::attention<float>(a, head_stride, as_stream(stream));
+      dn::attention<float>(a, head_stride, cus, as_stream(stream));
   });
 }
 

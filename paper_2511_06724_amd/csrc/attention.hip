@@ -707,7 +707,7 @@ template <typename T, int D, int NW> void launch(dim3 grid, const AttnParams& p,
 
 }  // namespace
 
-template <typename T> void attention(const AttnParams& p, int D, hipStream_t s) {
+template <typename T> void attention(const AttnParams& p, int D, int cus, hipStream_t s) {
   DN_CHECK(p.B >= 1 && p.heads >= 1 && p.Sq >= 1 && p.Skv >= 1, "attention: empty problem");
   DN_CHECK(D == 32 || D == 64, "attention: padded head dim must be 32 or 64");
   DN_CHECK(p.q && p.k && p.vt && p.o, "attention: null operand");
@@ -717,6 +717,8 @@ template <typename T> void attention(const AttnParams& p, int D, hipStream_t s) 
   // bf16, head dim 64: the software-pipelined kernel. Four waves (128 queries) per workgroup
   // share a key tile; the variant follows from how many such workgroups a CU gets, since the
   // CU with one more sets the time (measured, us, in the order below):
+  //  - up to half of one: two-wave workgroups with score read-ahead, one per CU and twice as many
+  //    (2 x 8 heads, 1024 keys 13.3, four waves 14.4; 2 x 20, 256 queries, 4096 keys 43.0, 45.7);
   //  - up to one: two waves per SIMD's registers (2 x 20 heads, 576 keys 10.1, three waves per
   //    SIMD 10.2, two-wave workgroups with score read-ahead 12.0; 2 x 10, 1024: 14.5, 15.0, 17.7);
   //  - up to 1.6: two-wave workgroups with read-ahead halve the uneven part (2 x 10, 1600: 28.2,
@@ -725,21 +727,24 @@ template <typename T> void attention(const AttnParams& p, int D, hipStream_t s) 
   //  - more: three waves per SIMD (2 x 10, 4096: 110.2, 102.1, 148.3; 4 x 20, 1024: 33.5, 30.7, 38.3).
   // Rings of three key tiles instead of two were no faster without read-ahead (107.9, 32.1).
   // Short key ranges (the 77 text tokens) take three waves per SIMD (2 x 10, 4096 queries: 11.9,
-  // 10.1, 13.1). fp32 and head dim 32 take the register-staged kernel below.
+  // 10.1, 13.1).
   if (sizeof(T) == 2 && D == 64) {
-    constexpr int kCus = 256;
-    const long long wgs = (long long)((p.Sq + 127) / 128) * p.heads * p.B;
-    if (p.Skv < 256 || wgs > 2 * kCus)
+    const long long heads = (long long)p.heads * p.B;
+    const long long wgs = (p.Sq + 127) / 128 * heads, half_wgs = (p.Sq + 63) / 64 * heads;
+    if (p.Skv < 256 || wgs > 2ll * cus)
       launch_pipe<4, 2, 3, false>(p, s);
-    else if (wgs > kCus && 10 * wgs <= 16 * kCus)
+    else if (half_wgs <= cus || (wgs > cus && 10 * wgs <= 16ll * cus))
       launch_pipe<2, 3, 2, true>(p, s);
     else
       launch_pipe<4, 2, 2, false>(p, s);
     DN_HIP(hipGetLastError());
     return;
   }
-  // fp32 and head dim 32 with fewer 64-query workgroups than CUs: the keys split over waves
-  if ((long long)((p.Sq + 63) / 64) * p.heads * p.B < 256) {
+  // fp32 and head dim 32 with fewer 64-query workgroups than CUs: the keys split over waves,
+  // from the shortest key ranges to long ones (fp32, head dim 64, against the kernel below, us:
+  // 2 x 8 heads, 960 queries and 77 keys 15.7 -> 10.0; 2 x 2, 4032 and as many 315 -> 179; one
+  // head, 16320 and as many 1260 -> 694)
+  if ((long long)((p.Sq + 63) / 64) * p.heads * p.B < cus) {
     if (D == 32)
       launch_keysplit<T, 32>(p, s);
     else if constexpr (sizeof(T) == 4)  // (bf16 with head dim 64 has returned)
@@ -747,8 +752,8 @@ template <typename T> void attention(const AttnParams& p, int D, hipStream_t s) 
     DN_HIP(hipGetLastError());
     return;
   }
-  // Fewer, wider workgroups when there are many queries; two waves per workgroup
-  // otherwise, so that short sequences still spread over every CU.
+  // The register-staged kernel: fewer, wider workgroups when there are many queries; two waves
+  // per workgroup otherwise, so that short sequences still spread over every CU.
   const long long wg4 = (long long)((p.Sq + 127) / 128) * p.heads * p.B;
   if (wg4 >= 512) {
     dim3 grid((p.Sq + 127) / 128, p.heads, p.B);
@@ -766,7 +771,7 @@ template <typename T> void attention(const AttnParams& p, int D, hipStream_t s) 
   DN_HIP(hipGetLastError());
 }
 
-template void attention<float>(const AttnParams&, int, hipStream_t);
-template void attention<bf16>(const AttnParams&, int, hipStream_t);
+template void attention<float>(const AttnParams&, int, int, hipStream_t);
+template void attention<bf16>(const AttnParams&, int, int, hipStream_t);
 
 }  // namespace dn

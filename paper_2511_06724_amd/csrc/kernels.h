@@ -109,7 +109,7 @@ struct AttnParams {
   int B = 0, heads = 0, Sq = 0, Skv = 0;
   float scale_log2 = 0.f;  // scale * log2(e)
 };
-template <typename T> void attention(const AttnParams& p, int D, hipStream_t s);
+template <typename T> void attention(const AttnParams& p, int D, int cus, hipStream_t s);
 
 // ---------------------------------------------------------------- norms
 // GroupNorm over NHWC [n][HW][c0 + c1] (two channel sources). Statistics in

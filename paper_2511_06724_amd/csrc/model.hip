@@ -955,7 +955,7 @@ template <typename T> struct Exec {
     a.Sq = Sq;
     a.Skv = Skv;
     a.scale_log2 = static_cast<float>(1.4426950408889634 / std::sqrt((double)x.D));
-    if (!dry) attention<T>(a, x.Dp, s);
+    if (!dry) attention<T>(a, x.Dp, m->cus, s);
   }
 
   // A residual-stream update R = (resid ? R : 0) + x W^T + b whose result is layer-normalised

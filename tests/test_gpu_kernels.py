@@ -253,11 +253,13 @@ def test_attention_few_queries(dtype, B, heads, Sq, Skv, d):
     test_attention(dtype, B, heads, Sq, Skv, d)
 
 
-@pytest.mark.parametrize("B,heads,Sq,Skv", [(2, 20, 300, 260), (5, 17, 385, 256), (6, 20, 300, 260), (8, 17, 385, 257),
+@pytest.mark.parametrize("B,heads,Sq,Skv", [(1, 1, 1, 256), (2, 5, 300, 321), (1, 64, 256, 300), (1, 64, 257, 300),
+                                            (2, 20, 300, 260), (5, 17, 385, 256), (6, 20, 300, 260), (8, 17, 385, 257),
                                             (8, 20, 300, 260), (9, 20, 300, 321)])
 def test_attention_variants(B, heads, Sq, Skv):
-    """The bf16 head-dim-64 kernel's variants (up to one, 1.6, two and more than two 128-query
-    workgroups per CU), with ragged query and key tails."""
+    """The bf16 head-dim-64 kernel's variants (up to half of one, one, 1.6, two and more than two
+    128-query workgroups per CU; 1 x 64 heads have the last size of the first and the next one),
+    with ragged query and key tails."""
     test_attention(dn.DN_BF16, B, heads, Sq, Skv, 64)
 
 
