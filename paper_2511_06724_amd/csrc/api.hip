@@ -218,6 +218,14 @@ void grow(float** buf, size_t* have, size_t need) {
   *have = need;
 }
 
+// Compute units of the current device (no allocation: callers may be capturing).
+int current_cus() {
+  int dev = 0, cus = 0;
+  DN_HIP(hipGetDevice(&dev));
+  DN_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+  return cus;
+}
+
 OpDev& op_dev_locked(int dev) {
   if ((int)g_op_dev.size() <= dev) g_op_dev.resize(dev + 1);
   OpDev& d = g_op_dev[dev];
@@ -572,9 +580,7 @@ dn_status dn_op_attention(int32_t dtype, const void* q, int32_t ldq, const void*
     a.Sq = Sq;
     a.Skv = Skv;
     a.scale_log2 = scale * 1.4426950408889634f;
-    int dev = 0, cus = 0;
-    DN_HIP(hipGetDevice(&dev));
-    DN_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    const int cus = current_cus();
     if (dtype == DN_BF16)
       dn::attention<dn::bf16>(a, head_stride, cus, as_stream(stream));
     else
@@ -637,6 +643,7 @@ dn_status dn_op_groupnorm(int32_t dtype, const void* x, void* y, int32_t n, int3
       ws = d.gn;
     }
     dn::GroupNormParams p;
+    p.cus = current_cus();
     p.x0 = x;
     p.c0 = C;
     p.n = n;

@@ -123,6 +123,7 @@ struct GroupNormParams {
   const float* beta = nullptr;
   float eps = 1e-5f;
   int silu = 0;
+  int cus = 0;  // compute units of the device
   void* y = nullptr;
   float* partial = nullptr;  // workspace, groupnorm_workspace_floats()
   float* stats = nullptr;    // workspace [2][n][C]: per-channel scale, then shift

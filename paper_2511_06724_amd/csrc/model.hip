@@ -905,6 +905,7 @@ template <typename T> struct Exec {
   void groupnorm_(const void* x0, int c0, const void* x1, int c1, int HW, const Norm& nm, float eps, bool silu,
                   void* y) {
     GroupNormParams p;
+    p.cus = m->cus;
     p.x0 = x0;
     p.x1 = x1;
     p.c0 = c0;

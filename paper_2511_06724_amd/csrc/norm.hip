@@ -421,11 +421,28 @@ __global__ __launch_bounds__(kGnOneThreads) void gn_one_kernel(GroupNormParams p
   }
 }
 
+// Whether the one-launch form is the faster one: `wgs` workgroups whose threads hold vpt vectors
+// of a slice of sv vectors and `groups` groups; pairs: the three launches would apply by
+// (pixel, vector) pairs. Measured against the three launches (us, three -> one):
+//  - slices of more than 32 bytes, up to a workgroup per CU and 6 vectors per thread: 8 x 1024 x
+//    640 fp32 16.3 -> 15.6; 2 x 2304 x 640 bf16 (12 vectors) 12.6 -> 17.2. Two per CU only with a
+//    short share each: 16 x 256 x 1280 bf16 gains, 16 x 576 is even, 16 x 1024 29.2 -> 33.1.
+//  - slices of 32 bytes (a quarter of each line a pixel's row touches): fewer workgroups the more
+//    each holds, 16 x 525 x 64 fp32 8.8 -> 5.2, 16 x 1700 x 128 12.5 -> 14.5; the sums of a slice
+//    of many groups take the longer the more groups its vectors are sorted into (bf16, eight
+//    groups: 2 x 2304 x 64 9.8 -> 10.5; sixteen: 2 x 1024 x 32 9.6 -> 11.3).
+//  - pairs: 2 x 1024 x 2560 bf16 20.0 -> 14.9, even at 24 samples.
+bool gn_one_faster(long long wgs, int vpt, int sv, int group_elems, bool pairs, int cus) {
+  if (pairs) return vpt <= kGnOneMaxVec;
+  if (sv <= 2) return group_elems <= 64 && vpt <= (group_elems <= 32 ? 6 : 4) && 4 * wgs * vpt <= 3ll * cus;
+  return wgs <= cus ? vpt <= 6 : wgs <= 2ll * cus && vpt <= 2;
+}
+
 // Slice geometry of the one-launch GroupNorm: groups per slice (0: does not apply).
 struct GnOne {
   int groups = 0, sv = 0, vpt = 0;
 };
-template <typename T> GnOne gn_one_geom(int HW, int C, int G) {
+template <typename T> GnOne gn_one_geom(int n, int HW, int C, int G, int cus) {
   constexpr int VEC = Elem<T>::kVec;
   const int cg = C / G;
   for (int g = 1; g <= G && g <= kGnOneMaxGroups; g *= 2) {
@@ -435,10 +452,7 @@ template <typename T> GnOne gn_one_geom(int HW, int C, int G) {
     const int sv = ch / VEC;
     if (sv > 64) break;
     const int pls = kGnOneThreads / sv, vpt = (HW + pls - 1) / pls;
-    // beyond 6 vectors per thread the few workgroups (groups x samples) take longer than the
-    // three launches over the whole chip (2 x 2304 x 640 bf16, 12: 17.2 us against 12.6),
-    // except where those walk (pixel, vector) pairs (2 x 1024 x 2560, 11: 14.9 against 20.0)
-    if (vpt > (C / VEC > 256 ? kGnOneMaxVec : 6)) break;
+    if (!gn_one_faster((long long)(G / g) * n, vpt, sv, g * VEC, C / VEC > 256, cus)) break;
     return GnOne{g, sv, vpt};
   }
   return GnOne{};
@@ -600,7 +614,7 @@ template <typename T> void groupnorm(const GroupNormParams& p, hipStream_t s) {
   DN_CHECK(C % p.G == 0, "groupnorm: channels must divide into groups");
   DN_CHECK(p.c0 % VEC == 0 && p.c1 % VEC == 0, "groupnorm: channel counts must be multiples of 16 bytes");
   DN_CHECK(p.x0 && p.y && p.partial && p.stats && p.gamma && p.beta && (p.c1 == 0 || p.x1), "groupnorm: null");
-  const GnOne one = gn_one_geom<T>(p.HW, C, p.G);
+  const GnOne one = gn_one_geom<T>(p.n, p.HW, C, p.G, p.cus);
   if (one.groups) {
     if (one.vpt <= 2)
       launch_gn_one<T, 2>(p, one, C, s);

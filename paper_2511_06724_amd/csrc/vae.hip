@@ -427,6 +427,7 @@ template <typename T> struct VaeExec {
       return;
     }
     GroupNormParams p;
+    p.cus = v->cus;
     p.x0 = x;
     p.c0 = C;
     p.n = n;

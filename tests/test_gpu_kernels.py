@@ -347,6 +347,16 @@ def test_groupnorm(dtype, n, HW, C, G, silu):
 
 
 @pytest.mark.parametrize("dtype", DT)
+@pytest.mark.parametrize("n,HW,C,G", [(8, 100, 320, 8), (17, 100, 320, 8), (9, 40, 640, 32), (9, 450, 640, 32), (17, 40, 640, 32),
+                                      (3, 1000, 32, 32), (2, 1700, 64, 32), (30, 400, 64, 32), (2, 60, 128, 128)])
+def test_groupnorm_forms(dtype, n, HW, C, G):
+    """Sizes around the lines between the one-launch and the three-launch form: one and two
+    workgroups per CU with short and longer shares, and 32-byte slices of one to sixteen
+    groups with few and many workgroups. Same bound as test_groupnorm."""
+    test_groupnorm(dtype, n, HW, C, G, 1)
+
+
+@pytest.mark.parametrize("dtype", DT)
 @pytest.mark.parametrize("M,C", [(300, 1280), (77, 64), (2048, 640)])
 def test_layernorm(dtype, M, C):
     announce(f"layernorm dtype={dtype} M={M} C={C}")
