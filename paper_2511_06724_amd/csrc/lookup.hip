@@ -242,9 +242,10 @@ __global__ __launch_bounds__(256) void reduce_kernel(const Cand* part, int nb, c
 
 constexpr int kBatchQ = 64;        // queries per pass: two 32-query halves
 constexpr int kBatchBlocks = 256;  // at most one workgroup per CU
-constexpr int kTileRows = 32;      // table rows per tile
 // dims per LDS stage; a tile takes at least two stages
 constexpr int stage_k(int dim) { return dim >= 512 ? 256 : 128; }
+// 256 dims: tables from this many rows on split a tile's rows over the waves, not its dims.
+constexpr int kRowSplitMin = 50000;
 
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
@@ -252,11 +253,14 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 // queries [32 qh, 32 qh + 32) over half kh of every stage's dims in registers (2 KS VGPRs: B
 // operands of the 32x32x16 f16 matrix-core step, lane l query l % 32, dims 16 s + 8 (l / 32)
 // ..), and the four waves score the group's 32-row tiles together: the kh = 1 halves of the
-// sums and norms reach the kh = 0 wave through LDS, which scores a tile one stage later. The
-// rows go global -> LDS in 512-byte (256 dims: 256-byte) pieces into a ring of R stages per group, swizzled
-// (16-byte chunk c of row r at position c ^ (r % 16)), so that the A operands are conflict-free
-// 16-byte LDS reads. A group's rows are contiguous; rows past its range read its last row and
-// are not scored.
+// sums and norms reach the kh = 0 wave through LDS, which scores a tile one stage later. ROWS: a
+// wave holds its queries over all dims and scores half kh of a 64-row tile. At 256 dims the
+// exchange and a barrier per 8 KB of rows cost long scans more than the longer query loads
+// (64 queries, dims split -> rows split: 300,000 rows 42.0 -> 39.1 us, 100,000 21.6 -> 20.3,
+// 30,000 12.4 -> 12.9, 2,000 8.7 -> 10.9). The rows go global -> LDS in 512-byte (256 dims: 256-byte) pieces into a ring
+// of R stages per group, swizzled (16-byte chunk c of row r at position c ^ (r % 16)), so that
+// the A operands are conflict-free 16-byte LDS reads. A group's rows are contiguous; rows past
+// its range read its last row and are not scored.
 // Bound by HBM (the table once per 64 queries). The previous form loaded the A operands
 // straight from the table (64-byte pieces of 16 rows per load, half a line each) and re-read
 // every query operand from LDS per 16-row tile, which its loads did not hide: 48.0 us for
@@ -265,37 +269,42 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 constexpr int kBatchGroups = 2, kBatchWaves = 4 * kBatchGroups;
 constexpr int kRingBytes = 64 * 1024;  // per group
 
-template <int KS>
+template <int KS, bool ROWS>
 __global__ __launch_bounds__(kBatchWaves * 64) void scan_mfma_kernel(const uint16_t* q, int nq, const uint16_t* cache,
                                                                      int n, Cand* part) {
   constexpr int NG = kBatchGroups;
   constexpr int dim = 16 * KS, SK = stage_k(dim), ST = dim / SK;  // stages per tile
   constexpr int RB = 2 * SK;                                      // bytes of a row per stage
-  constexpr int SB = kTileRows * RB, R = kRingBytes / SB;         // bytes per stage, ring depth
-  constexpr int HS = SK / 32;                                     // k-steps per wave and stage
+  constexpr int TR = ROWS ? 64 : 32;                              // rows per tile
+  constexpr int SB = TR * RB, R = kRingBytes / SB;                // bytes per stage, ring depth
+  constexpr int HS = ROWS ? SK / 16 : SK / 32;                   // k-steps per wave and stage
   constexpr int CPR = RB / 16, RPI = 64 / CPR;                    // 16-byte chunks per row, rows per DMA
-  constexpr int NI = 8 / RPI;                                     // DMA instructions per wave and stage
+  constexpr int DR = TR / 4, NI = DR / RPI;                       // rows, DMA instructions per wave and stage
   static_assert(ST >= 2, "the partial sums of a tile are read before the next tile's are written");
-  extern __shared__ __align__(16) unsigned char ring[];  // [group][R][32 rows][RB]
-  __shared__ float half_acc[NG][2][16][64];
-  __shared__ float half_cc[NG][2][kTileRows];
-  __shared__ float inv[NG][2][kTileRows];
-  __shared__ Cand red[NG][kBatchQ];
+  constexpr int NR = ROWS ? 2 * NG : NG;                // winners per query to merge
+  extern __shared__ __align__(16) unsigned char ring[];  // [group][R][TR rows][RB]
+  __shared__ float half_acc[ROWS ? 1 : NG][2][16][64];
+  __shared__ float half_cc[NG][2][32];
+  __shared__ float inv[NG][4][32];
+  __shared__ Cand red[NR][kBatchQ];
   const int t = threadIdx.x, lane = t & 63;
   const int w = __builtin_amdgcn_readfirstlane(t >> 6);
   const int grp = w >> 2, qh = w & 1, kh = (w >> 1) & 1;
   const int r32 = lane & 31, h = lane >> 5;
+  const int rb = ROWS ? 32 * kh : 0;         // the wave's first row of a tile
+  const int dk = ROWS ? 0 : HS * kh;         // and its first k-step of a stage
+  const bool scores = ROWS || kh == 0;
   // this group's rows [row0, row1): equal contiguous shares
   const int shares = (int)gridDim.x * NG, per = n / shares + (n % shares != 0);
   const long long begin = (long long)(blockIdx.x * NG + grp) * per;
   const int row0 = (int)(begin < n ? begin : n), row1 = (int)(begin + per < n ? begin + per : n);
-  const int tiles = (per + kTileRows - 1) / kTileRows;  // the same for every group: barriers match
+  const int tiles = (per + TR - 1) / TR;  // the same for every group: barriers match
   const int total = tiles * ST;
 
   // DMA of stage g (tile g / ST, dims [SK (g % ST), + SK)): wave j of the group loads rows
-  // [8 j, 8 j + 8), RPI per instruction; stages past the end repeat the last one
+  // [DR j, DR j + DR), RPI per instruction; stages past the end repeat the last one
   unsigned char* const gring = ring + grp * kRingBytes;
-  const int drow = 8 * (w & 3) + lane / CPR;
+  const int drow = DR * (w & 3) + lane / CPR;
   const int last_row = row1 > 0 ? row1 - 1 : 0;
   int dg = 0, dbase = row0 < last_row ? row0 : last_row, dst = 0;  // next stage, its tile's first row, its dims
   auto issue = [&]() {
@@ -306,11 +315,11 @@ __global__ __launch_bounds__(kBatchWaves * 64) void scan_mfma_kernel(const uint1
     for (int j = 0; j < NI; ++j) {
       const int row = drow + RPI * j;
       const unsigned off = (unsigned)min(row, lim) * (2 * dim) + (unsigned)(((lane % CPR) ^ (row & 15)) * 16);
-      dma16_base(src, off, (lds_void*)(slot + (8 * (w & 3) + RPI * j) * RB));
+      dma16_base(src, off, (lds_void*)(slot + (DR * (w & 3) + RPI * j) * RB));
     }
     ++dg;
     const bool more = dg < total, wrap = dst + 1 == ST;
-    dbase = more && wrap ? min(dbase + kTileRows, last_row) : dbase;
+    dbase = more && wrap ? min(dbase + TR, last_row) : dbase;
     dst = more ? (wrap ? 0 : dst + 1) : dst;
   };
 #pragma unroll
@@ -319,7 +328,7 @@ __global__ __launch_bounds__(kBatchWaves * 64) void scan_mfma_kernel(const uint1
   f16x8 qf[ST * HS];
   {
     const int qi = 32 * qh + r32;
-    const uint16_t* qp = q + (long long)(qi < nq ? qi : 0) * dim + 16 * HS * kh + 8 * h;
+    const uint16_t* qp = q + (long long)(qi < nq ? qi : 0) * dim + 16 * dk + 8 * h;
 #pragma unroll
     for (int s = 0; s < ST * HS; ++s)
       qf[s] = *reinterpret_cast<const f16x8*>(qp + (s / HS) * SK + 16 * (s % HS));
@@ -335,17 +344,17 @@ __global__ __launch_bounds__(kBatchWaves * 64) void scan_mfma_kernel(const uint1
   float cc[2] = {0.f, 0.f}, prev_cc = 0.f;
 #pragma unroll
   for (int r = 0; r < 16; ++r) acc[0][r] = acc[1][r] = prev[r] = 0.f;
-  // kh = 0: adds the other half of tile `tile` (in LDS) to prev and scores it
+  // scores the wave's rows of tile `tile` from prev (dims split: plus the other half, in LDS)
   auto finish = [&](int tile) {
-    const float c2 = prev_cc + half_cc[grp][qh][r32];
-    inv[grp][qh][r32] = c2 > 0.f ? rsqrtf(c2) : -1.f;  // 1 / |c| of row r32, -1 for a zero row
-    const int base = tile * kTileRows;
+    const float c2 = ROWS ? prev_cc : prev_cc + half_cc[grp][qh][r32];
+    inv[grp][w & 3][r32] = c2 > 0.f ? rsqrtf(c2) : -1.f;  // 1 / |c| of row r32, -1 for a zero row
+    const int base = tile * TR + rb;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       // c_row . q_(32 qh + r32), row = 8 (r / 4) + 4 h + r % 4: rows ascend with r
       const int rr = 8 * (r >> 2) + 4 * h + (r & 3);
-      const float iv = inv[grp][qh][rr];
-      const float dot = prev[r] + half_acc[grp][qh][r][lane];
+      const float iv = inv[grp][w & 3][rr];
+      const float dot = ROWS ? prev[r] : prev[r] + half_acc[grp][qh][r][lane];
       const float sc = iv > 0.f ? dot * iv : -INFINITY;
       if (base + rr < row1 - row0 && sc > best_s) {
         best_s = sc;
@@ -364,10 +373,10 @@ __global__ __launch_bounds__(kBatchWaves * 64) void scan_mfma_kernel(const uint1
       __builtin_amdgcn_s_barrier();
       __builtin_amdgcn_sched_barrier(0);
       issue();
-      const unsigned char* slot = gring + (g % R) * SB + r32 * RB;
+      const unsigned char* slot = gring + (g % R) * SB + (rb + r32) * RB;
 #pragma unroll
       for (int s = 0; s < HS; ++s) {
-        const f16x8 a = *reinterpret_cast<const f16x8*>(slot + (((2 * (HS * kh + s) + h) ^ (r32 & 15)) * 16));
+        const f16x8 a = *reinterpret_cast<const f16x8*>(slot + (((2 * (dk + s) + h) ^ (r32 & 15)) * 16));
         acc[s & 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, qf[st * HS + s], acc[s & 1], 0, 0, 0);
         const uint4 u = __builtin_bit_cast(uint4, a);
         const unsigned wd[4] = {u.x, u.y, u.z, u.w};
@@ -377,13 +386,13 @@ __global__ __launch_bounds__(kBatchWaves * 64) void scan_mfma_kernel(const uint1
       // the norm's terms are taken here (the compiler would sink them to the tile's end and
       // keep every operand until then)
       asm volatile("" : "+v"(cc[0]), "+v"(cc[1]));
-      if (st == 0 && kh == 0 && tile > 0) finish(tile - 1);
+      if (st == 0 && scores && tile > 0) finish(tile - 1);
       __builtin_amdgcn_sched_barrier(0);
     }
     prev = acc[0] + acc[1];
     prev_cc = cc[0] + cc[1];
     prev_cc += __shfl_xor(prev_cc, 32, 64);
-    if (kh == 1) {
+    if (!scores) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) half_acc[grp][qh][r][lane] = prev[r];
       half_cc[grp][qh][r32] = prev_cc;
@@ -394,7 +403,7 @@ __global__ __launch_bounds__(kBatchWaves * 64) void scan_mfma_kernel(const uint1
   }
   __builtin_amdgcn_s_waitcnt(wait_vm_lgkm0(0));
   __syncthreads();
-  if (kh == 0) {
+  if (scores) {
     finish(tiles - 1);
     // the two lane halves of a query
     const float s2 = __shfl_xor(best_s, 32, 64);
@@ -403,12 +412,12 @@ __global__ __launch_bounds__(kBatchWaves * 64) void scan_mfma_kernel(const uint1
       best_s = s2;
       best_i = i2;
     }
-    if (h == 0) red[grp][32 * qh + r32] = Cand{best_s, best_i};
+    if (h == 0) red[ROWS ? 2 * grp + kh : grp][32 * qh + r32] = Cand{best_s, best_i};
   }
   __syncthreads();
   if (t < kBatchQ) {
     Cand b = red[0][t];
-    for (int k = 1; k < NG; ++k)
+    for (int k = 1; k < NR; ++k)
       if (better(red[k][t].s, red[k][t].i, b.s, b.i)) b = red[k][t];
     part[(long long)blockIdx.x * kBatchQ + t] = b;
   }
@@ -464,19 +473,19 @@ __global__ __launch_bounds__(256) void reduce_batch_kernel(const Cand* part, int
 
 // Launches the scan over at most 256 workgroups, each group with at least a tile's rows where
 // the table has them; returns that count.
-template <int KS>
+template <int KS, bool ROWS = false>
 int launch_batch(const uint16_t* q, int nq, const uint16_t* cache, int n, Cand* part, hipStream_t s) {
-  const int rows = kTileRows * kBatchGroups;
+  const int rows = (ROWS ? 64 : 32) * kBatchGroups;
   const int want = n / rows + (n % rows != 0);
   const int nb = want < kBatchBlocks ? want : kBatchBlocks;
   const size_t lds = (size_t)kBatchGroups * kRingBytes;
   static bool attr = false;  // per process: the attribute belongs to the code object
   if (!attr) {
-    DN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&scan_mfma_kernel<KS>),
+    DN_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&(scan_mfma_kernel<KS, ROWS>)),
                                hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)));
     attr = true;
   }
-  hipLaunchKernelGGL(scan_mfma_kernel<KS>, dim3(nb), dim3(kBatchWaves * 64), lds, s, q, nq, cache, n, part);
+  hipLaunchKernelGGL((scan_mfma_kernel<KS, ROWS>), dim3(nb), dim3(kBatchWaves * 64), lds, s, q, nq, cache, n, part);
   return nb;
 }
 
@@ -536,7 +545,10 @@ void lookup_batch(const uint16_t* q, int nq, const uint16_t* cache, long long n,
   Cand* part = static_cast<Cand*>(ws);
   int nb = 0;
   switch (dim) {
-    case 256: nb = launch_batch<16>(q, nq, cache, n32, part, s); break;
+    case 256:
+      nb = n32 >= kRowSplitMin ? launch_batch<16, true>(q, nq, cache, n32, part, s)
+                               : launch_batch<16>(q, nq, cache, n32, part, s);
+      break;
     case 512: nb = launch_batch<32>(q, nq, cache, n32, part, s); break;
     case 768: nb = launch_batch<48>(q, nq, cache, n32, part, s); break;
     default: nb = launch_batch<64>(q, nq, cache, n32, part, s); break;

@@ -105,7 +105,8 @@ def test_batch_planted_full_cache():
 
 @pytest.mark.parametrize("nq,n,dim", [(1, 1, 768), (5, 17, 256), (64, 1001, 512), (70, 4097, 768),
                                       (3, 300, 1024), (2, 15, 768), (7, 200, 77), (9, 33, 1536),
-                                      (8, 60001, 256), (4, 40003, 512), (5, 70001, 1024)])
+                                      (8, 60001, 256), (4, 40003, 512), (5, 70001, 1024),
+                                      (2, 1, 256), (64, 64, 256), (33, 129, 256), (64, 49999, 256), (64, 50000, 256), (64, 90113, 256)])
 def test_batch_ragged_sizes_zero_rows_and_queries(nq, n, dim):
     announce(f"lookup batch: nq={nq} n={n} dim={dim}")
     rng = np.random.default_rng(nq * 1000 + n + dim)
@@ -154,6 +155,24 @@ def test_batch_duplicates_give_lowest_index_and_errors_touch_nothing():
     assert dn.lib.ac_lookup_batch(None, 2, 1, 5, 768, out, None) == dn.DN_EINVAL
     assert dn.lib.ac_lookup_batch(1, 0, 1, 5, 768, out, None) == dn.DN_EINVAL
     assert list(out) == [-7, -7]
+
+
+@pytest.mark.parametrize("n,dim", [(9000, 256), (60_000, 256), (9000, 512), (9000, 768), (9000, 1024)])
+def test_batch_duplicates_across_waves_and_workgroups(n, dim):
+    """Equal rows in both halves of a tile, in neighbouring tiles and in other workgroups, for
+    every width of the batched scan and both splits at 256 dims: the lowest index wins, for queries of either half."""
+    announce(f"lookup batch: duplicates, {n} x {dim}")
+    rng = np.random.default_rng(dim)
+    cache = rng.standard_normal((n, dim)).astype(np.float16)
+    qs = rng.standard_normal((64, dim)).astype(np.float16)
+    for j in range(64):
+        first = int(rng.integers(0, 4000))
+        for at in (first, first + 1, first + 32, first + 33, first + 64, first + n // 3, n - 1 - j):
+            cache[at] = qs[j]
+    # later plants may have overwritten earlier ones: the oracle says what is left
+    ref = [int(np.flatnonzero((cache == q).all(axis=1))[0]) for q in qs]
+    idx, _ = dn.ac_lookup_batch(_dev16(qs), _dev16(cache))
+    assert list(idx) == ref
 
 
 # ----------------------------------------------------------------------------- similarity-driven K
