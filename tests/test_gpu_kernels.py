@@ -20,6 +20,7 @@ import torch
 
 from oracle import layers as L
 from paper_2511_06724_amd import dn
+from tests import plans as P
 from tests.gpu_util import DEV, announce, f32_dev, host, rel_l2, tdtype, to_dev
 
 pytestmark = pytest.mark.gpu
@@ -38,16 +39,12 @@ def _rng(seed):
                                    (1000, 640, 5120), (129, 256, 704), (2000, 1248, 1280), (8000, 608, 2560),
                                    (8192, 200, 256), (16384, 640, 1280), (2048, 10240, 1280), (16300, 608, 1280)])
 def test_linear(dtype, M, N, K):
-    """Shapes cover every tile plan: in fp32 the register-staged 64 x 64 / 128 x 128
-    tiles; in bf16 the row-major kernels for N % 32 != 0 (N = 200) and the fragment-B
-    kernel with 128 x 128 and 128 x 256 tiles, with and without split-K (few tiles and
-    long K: 300 x 1280 x 2560, 1000 x 640 x 5120), the five-wave 64 x 160 and 128 x 160
-    tiles (2000 x 1248 x 1280, 8000 x 608 x 2560: one tile per CU, ragged last row tile
-    and column tile), ragged M and N tails; a tall row-major case (8192 x 200 x 256); the
-    four-wave 128 x 160 tiles, two per CU, that linear layers with more 160-column tiles
-    than CUs take (16384 x 640 x 1280, 2048 x 10240 x 1280; 16300 x 608 x 1280 with a ragged
-    last row tile and column tile). Outputs: bf16 / fp32 without residual, fp32
-    with an fp32 residual, and the op's dtype with a residual in that dtype."""
+    """Linear layers of many sizes, ragged in rows and columns, short and long in K: in fp32 the
+    register-staged 64 x 64 / 128 x 128 tiles and the wave-split 32-column ones, in bf16 the
+    row-major kernels for N % 32 != 0 (N = 200; tall at 8192 x 200 x 256) and the fragment-B
+    kernels (test_every_tile_plan has one shape per tile and split of those). Outputs: bf16 /
+    fp32 without residual, fp32 with an fp32 residual, and the op's dtype with a residual in
+    that dtype."""
     announce(f"linear dtype={dtype} M={M} N={N} K={K}")
     r = _rng(M + N + K)
     x, xh = to_dev(r.standard_normal((M, K)), dtype)
@@ -102,6 +99,59 @@ def test_linear_epilogue_forms(M, N, K, off):
             torch.cuda.synchronize()
             assert rel_l2(host(y).reshape(M, N), want) < (1e-5 if yt == torch.float32 else TOL[dn.DN_BF16]), (rt, yt)
             assert (buf[off + M * N:].float() == 7).all() and (buf[:off].float() == 7).all()
+
+
+@pytest.mark.parametrize("kind,M,N,K,geglu,out_f32", sorted(P.COVER))
+def test_every_tile_plan(kind, M, N, K, geglu, out_f32):
+    """Every tile of the fragment-B kernels, whole and with K split, on a shape with a ragged
+    last row tile and a ragged last column tile (that the plan is the one meant is checked on
+    the host). fp32 outputs with an fp32 residual: fp32 sums of at most 10240 products against
+    64 bits, 1e-5; bf16 outputs one rounding (TOL). Nothing past the output is written."""
+    want = P.COVER[kind, M, N, K, geglu, out_f32]
+    g = P.plan(M, N, K, kind, geglu=geglu, out_f32=out_f32)
+    assert (g.bm, g.bn, g.x5, g.split) == want
+    if geglu:
+        return test_fp8_linear(M, N // 2, K, True, False) if kind == P.FP8 else test_linear_geglu(dn.DN_BF16, M, N // 2, K)
+    if kind == P.FP8:
+        return test_fp8_linear(M, N, K, False, True)
+    if kind == P.CONV:
+        n, H, W = P.CONV_IMAGES[M]
+        return test_conv3x3(dn.DN_BF16, n, H, W, K // 9, N, 0, 1)
+    if kind == P.VT:
+        heads = max(1, N // 96)
+        dp = 16 if N == 32 else 32
+        return test_linear_vt_splits(dn.DN_BF16, M, M // 2 if M < 100 else 475 if M == 1900 else 500, N, N - heads * dp,
+                                     heads, dp, K)
+    announce(f"tile plan {want}: linear {M} x {N} x {K}")
+    r = _rng(M + N + K)
+    x, xh = to_dev(r.standard_normal((M, K)), dn.DN_BF16)
+    w, wh = to_dev(r.standard_normal((N, K)) / math.sqrt(K), dn.DN_BF16)
+    b = r.standard_normal(N).astype(np.float32)
+    res = r.standard_normal((M, N)).astype(np.float32) if out_f32 else None
+    buf = torch.full((M * N + 64,), 7.0, device=DEV, dtype=torch.float32 if out_f32 else torch.bfloat16)
+    dn.op_linear(dn.DN_BF16, x, dn.pack_weight(dn.DN_BF16, w, N, K), f32_dev(b), buf, M, N, K,
+                 resid=f32_dev(res) if out_f32 else None, resid_f32=True, y_f32=out_f32)
+    torch.cuda.synchronize()
+    ref = L.linear(xh, wh, b.astype(np.float64)) + (res if out_f32 else 0.0)
+    assert rel_l2(host(buf[:M * N]).reshape(M, N), ref) < (1e-5 if out_f32 else TOL[dn.DN_BF16])
+    assert (buf[M * N:].float() == 7).all()
+
+
+@pytest.mark.parametrize("kind,M,N,K,geglu,out_f32", [k for k, v in sorted(P.COVER.items()) if v[3] > 1 and k[0] in (P.LINEAR, P.FP8)])
+def test_split_k_is_deterministic(kind, M, N, K, geglu, out_f32):
+    """Split plans twice: bitwise equal (the parts are summed in split order)."""
+    announce(f"split-K twice: kind {kind} {M} x {N} x {K}")
+    g = torch.Generator(device=DEV).manual_seed(M + N + K)
+    x = torch.randn((M, K), device=DEV, generator=g)
+    w = torch.randn((N, K), device=DEV, generator=g) / math.sqrt(K)
+    t = dn.DN_FP8 if kind == P.FP8 else dn.DN_BF16
+    x = x.to(torch.float8_e4m3fn).view(torch.uint8) if t == dn.DN_FP8 else x.to(torch.bfloat16)
+    wp = dn.pack_weight(t, w if t == dn.DN_FP8 else w.to(torch.bfloat16), N, K)
+    ys = [torch.empty((M, N), device=DEV) for _ in range(2)]
+    for y in ys:
+        dn.op_linear(t, x, wp, None, y, M, N, K, y_f32=True)
+    torch.cuda.synchronize()
+    assert torch.equal(*ys) and ys[0].isfinite().all()
 
 
 @pytest.mark.parametrize("M,N,K", [(1, 4, 32), (33, 30, 32), (31, 100, 96), (70, 33, 64), (512, 64, 576), (1000, 65, 160),
@@ -169,8 +219,7 @@ def test_conv3x3(dtype, n, H, W, Cin, Cout, up, stride):
     """Small shapes with ragged tiles, and the SD-XL convolutions at full size, whole
     output against the oracle: the 128x128-level ResBlock convolutions (32768 rows, 320
     channels from 320 and from a 640-channel input) and the nearest-x2 upsampling
-    convolution into that level (640 channels): in bf16 these run on the four-wave
-    160-column tiles, two workgroups per CU; 2 x 100 x 100 has a ragged last row tile."""
+    convolution into that level (640 channels); 2 x 100 x 100 has a ragged last row tile."""
     announce(f"conv dtype={dtype} n={n} H={H} W={W} Cin={Cin} Cout={Cout} up={up} stride={stride}")
     r = _rng(n * H * W + Cin + Cout + up + stride)
     x, xh = to_dev(r.standard_normal((n, H, W, Cin)), dtype)
@@ -510,9 +559,8 @@ def test_sdxl_self_attention_sampled():
 @pytest.mark.parametrize("M,N,K", [(2048, 1280, 5120), (2048, 1280, 1280), (2048, 3840, 1280), (154, 2560, 2048)])
 def test_sdxl_linear_shapes_sampled_and_deterministic(M, N, K):
     """The M = 2048 projections of the SD-XL 32x32 blocks (FF-out, attention out, QKV)
-    and the context K/V projection, in the launch configuration the denoiser uses
-    (split-K where the planner picks it): sampled outputs against fp64 dot products,
-    and two launches bitwise equal (the split-K reduction order is fixed)."""
+    and the context K/V projection: sampled outputs against fp64 dot products, and two
+    launches bitwise equal (test_split_k_is_deterministic has the split plans)."""
     announce(f"sdxl linear {M}x{N}x{K}")
     g = torch.Generator(device=DEV).manual_seed(M + N + K)
     x = torch.randn((M, K), device=DEV, generator=g).to(torch.bfloat16)

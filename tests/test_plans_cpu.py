@@ -3,7 +3,7 @@ name kernels that run, and the shapes of the GPU operator tests reach every kern
 
 import pytest
 
-from tests.plans import CONV, FP8, LINEAR, VT, plan, plan_fp32
+from tests.plans import CONV, COVER, FP8, LINEAR, VT, plan, plan_fp32
 
 
 def test_vt_output_never_plans_a_kernel_that_does_not_run():
@@ -16,6 +16,26 @@ def test_vt_output_never_plans_a_kernel_that_does_not_run():
                 assert (g.x5, g.split, g.frag) == (0, 1, 1), (n * tokens, heads, K)
     # the same sizes without V^T do use it
     assert any(plan(2 * t, 960, 320, LINEAR).x5 for t in range(64, 4200, 31))
+
+
+def test_gpu_shapes_reach_every_kernel():
+    """The shapes of the GPU operator tests take the tile and split each is there for, and
+    together every tile, split and unsplit, that some shape of a wide range is given."""
+    for (kind, M, N, K, geglu, out_f32), want in COVER.items():
+        g = plan(M, N, K, kind, geglu=geglu, out_f32=out_f32)
+        assert (g.bm, g.bn, g.x5, g.split) == want, (kind, M, N, K)
+        assert M % g.bm and N % g.bn, "ragged tiles"
+    have = {(k[0], v[0], v[1], v[2], v[3] > 1, k[4]) for k, v in COVER.items()}
+    for kind in (LINEAR, VT, CONV, FP8):
+        for geglu in ((False, True) if kind in (LINEAR, FP8) else (False,)):
+            for M in (33, 154, 512, 1000, 2048, 2100, 4096, 8192, 12000, 16384, 32768, 262144):
+                for N in (64, 128, 320, 512, 640, 1280, 1920, 2560, 3840, 10240):
+                    for K in (128, 320, 640, 1280, 2560, 2880, 5120, 5760, 11520, 23040):
+                        if K % 64 or (kind == FP8 and K % 128):
+                            continue
+                        for out_f32 in (False, True):
+                            g = plan(M, N, K, kind, geglu=geglu, out_f32=out_f32)
+                            assert (kind, g.bm, g.bn, g.x5, g.split > 1, geglu) in have, (M, N, K)
 
 
 @pytest.mark.parametrize("M,N,K,want,us,other", [
