@@ -25,10 +25,7 @@ namespace dn {
 namespace {
 
 constexpr int kKT = 64;          // keys per LDS tile
-typedef __attribute__((address_space(3))) void lds_void_t;
 typedef __attribute__((address_space(1))) void gbl_void_t;
-// s_waitcnt immediate: vmcnt <= vm, lgkmcnt <= 0, expcnt unconstrained.
-constexpr int attn_wait_vm_lgkm0(int vm) { return (vm & 0xF) | (((vm >> 4) & 3) << 14) | (7 << 4); }
 constexpr float kLazy = 8.0f;    // log2 headroom before the reference max moves
 
 // 2^x with the hardware exponential (v_exp_f32): arguments here are <= kLazy, and
@@ -461,7 +458,7 @@ __global__ __launch_bounds__(64 * NQ) __attribute__((amdgpu_waves_per_eu(WPE, WP
 #pragma unroll
     for (int j = 0; j < PW; ++j) {
       const int i = wave * PW + j;
-      __builtin_amdgcn_global_load_lds((gbl_void_t*)(gbase + goff[j]), (lds_void_t*)(smem + slot * TILE + i * 1024), 16,
+      __builtin_amdgcn_global_load_lds((gbl_void_t*)(gbase + goff[j]), (lds_void*)(smem + slot * TILE + i * 1024), 16,
                                        0, 0);
     }
     if (next_issue < ntiles - 1) {
@@ -603,7 +600,7 @@ __global__ __launch_bounds__(64 * NQ) __attribute__((amdgpu_waves_per_eu(WPE, WP
 #pragma unroll
   for (int t = 0; t < R - 1; ++t) issue(t);
   if (PIPE) {
-    __builtin_amdgcn_s_waitcnt(attn_wait_vm_lgkm0((R - 2) * PW));
+    __builtin_amdgcn_s_waitcnt(wait_vm_lgkm0((R - 2) * PW));
     __builtin_amdgcn_s_barrier();
     bf16x8 kf[2][4];
     load_k(smem, kf);
@@ -622,7 +619,7 @@ __global__ __launch_bounds__(64 * NQ) __attribute__((amdgpu_waves_per_eu(WPE, WP
     for (int j = 0; j < U; ++j) {
       const int g = g0 + j;
       if (g < ntiles) {
-        __builtin_amdgcn_s_waitcnt(attn_wait_vm_lgkm0((PIPE ? R - 3 : R - 2) * PW));
+        __builtin_amdgcn_s_waitcnt(wait_vm_lgkm0((PIPE ? R - 3 : R - 2) * PW));
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
         issue((j + R - 1) % R);
@@ -650,7 +647,7 @@ __global__ __launch_bounds__(64 * NQ) __attribute__((amdgpu_waves_per_eu(WPE, WP
       }
     }
   }
-  __builtin_amdgcn_s_waitcnt(attn_wait_vm_lgkm0(0));
+  __builtin_amdgcn_s_waitcnt(wait_vm_lgkm0(0));
 
   l_run += partner(l_run);  // each half has summed its own keys
   const int qi = q0 + (lane & 31);
