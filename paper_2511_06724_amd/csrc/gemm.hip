@@ -396,7 +396,7 @@ template <typename T, bool CONV> void dispatch(const GemmParams& p, const GemmPl
 }  // namespace
 
 // Fragment-B kernels: tile, split and tail bands by a cost model fitted to launches measured
-// on MI355X (every tile and split of 804 shapes; weights from HBM, activations as the launch
+// on MI355X (every tile and split of some 800 shapes; weights from HBM, activations as the launch
 // before leaves them). A tile variant runs up to `wg` workgroups per CU; with c of them on the
 // busiest CU a K stage (64 bf16 or 128 fp8 values) takes stage[c - 1] us, so a round of units
 // costs fixed + wgcost c + stages x stage[c - 1], a grid is its full rounds plus the

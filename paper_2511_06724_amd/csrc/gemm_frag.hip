@@ -73,8 +73,9 @@ __device__ __forceinline__ bool aligned16(const void* q) {
 //
 // What bounds it: every workgroup of a launch reaches its epilogue together and runs every
 // instruction of it once, so its time is instruction fetch and the store burst. Hence one
-// short path per kind of output. The previous form (through LDS, one path with run-time cases
-// and element-wise tails, about 25,000 instructions) took 5.1 us of a 128 x 128 tile's launch
+// short path per kind of output (the kernels hold every kind, chosen at run time; a launch
+// fetches one). The previous form, one long path through LDS with run-time cases and
+// element-wise tails in it, took 5.1 us of a 128 x 128 tile's launch
 // and 13 us of a lone 128 x 256 tile's; measured whole launches, before -> after: QKV
 // 2048 x 3840 x 1280 32.3 -> 28.2 us, projection 2048 x 1280 x 1280 with an fp32 residual
 // 20.1 -> 17.8 us, FF-in 66.6 -> 63.1 us, 32768-row convolution 320 -> 320 77.9 -> 72.7 us.
