@@ -435,10 +435,10 @@ static const TileCost kConvCost[] = {{128, 256, 0, 2, 1.957, 0.0, {0.941, 1.549}
                                      {128, 128, 0, 2, 2.370, 0.0, {0.647, 1.019}, 0.278},
                                      {64, 128, 0, 4, 1.522, 0.034, {0.402, 0.600, 0.962, 1.171}, 0.278},
                                      {128, 160, 1, 2, 3.905, 0.0, {0.662, 1.110}, 0.315}};
-// fp8: 16384 x 320 x 1280 as 128 x 128 tiles (26.7 us as 128 x 256, so 24.0), 1152 x 320 x 1280 in
-// two parts (13.6, so 10.9).
-static const TileCost kFp8Cost[] = {{128, 256, 0, 2, 8.051, 0.0, {0.954, 1.196}, 0.144},
-                                    {128, 128, 0, 2, 4.941, 0.0, {0.648, 0.744}, 0.239}};
+// fp8: 16384 x 320 x 1280 as 128 x 128 tiles (20.5 us; 24.0 as 128 x 256), 1152 x 320 x 1280
+// in three parts (11.1; 11.9 whole), 2048 rows whole (12.0; 13.0 in two parts).
+static const TileCost kFp8Cost[] = {{128, 256, 0, 2, 7.559, 0.0, {0.928, 1.185}, 0.144},
+                                    {128, 128, 0, 2, 2.976, 0.0, {0.675, 0.765}, 0.267}};
 
 // by PlanKind; reduce in us, reduce_mb in us per MB (slabs read, outputs written)
 struct PlanCost {
@@ -449,7 +449,7 @@ struct PlanCost {
 static const PlanCost kPlanCost[] = {{kLinCost, 6, 3.5, 1 / 6.0},
                                      {kVtCost, 5, 0.0, 0.0},  // never split
                                      {kConvCost, 4, 5.745, 0.011},
-                                     {kFp8Cost, 2, 1.374, 0.164}};
+                                     {kFp8Cost, 2, 2.019, 0.206}};
 
 GemmPlan frag_plan(int M, int N, int K, int geglu, int cus, bool fused_reduce, PlanKind kind, bool out_f32) {
   const PlanCost& cost = kPlanCost[kind];

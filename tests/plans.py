@@ -60,8 +60,8 @@ COVER = {
     (CONV, 5000, 1184, 576, False, False): (128, 256, 0, 1),
     (CONV, 1500, 1312, 2880, False, False): (128, 256, 0, 3),
     (FP8, 33, 32, 128, False, True): (128, 128, 0, 1),
-    (FP8, 33, 32, 640, False, True): (128, 128, 0, 2),
-    (FP8, 20000, 224, 128, False, True): (128, 256, 0, 1),
+    (FP8, 33, 32, 1280, False, True): (128, 128, 0, 5),
+    (FP8, 8000, 608, 128, False, True): (128, 256, 0, 1),
     (FP8, 33, 64, 128, True, False): (128, 256, 0, 1),
     (FP8, 12000, 160, 10240, False, True): (128, 256, 0, 5),
 }

@@ -52,8 +52,9 @@ def test_convolution_plans_are_the_measured_best(M, N, K, want, us, other):
 
 
 @pytest.mark.parametrize("M,N,K,want,us,other", [
-    (16384, 320, 1280, (128, 128, 1), 24.0, "128 x 256 26.7"),
-    (1152, 320, 1280, (128, 128, 3), 10.9, "unsplit 13.6"),
+    (16384, 320, 1280, (128, 128, 1), 20.5, "128 x 256 24.0"),
+    (1152, 320, 1280, (128, 128, 3), 11.1, "unsplit 11.9"),
+    (2048, 320, 1280, (128, 128, 1), 12.0, "two parts 13.0"),
 ])
 def test_fp8_plans_are_the_measured_best(M, N, K, want, us, other):
     """Feed-forward outputs of 320 channels with an fp32 residual (as above)."""
